@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "cs_icdf_table.h"
 #include "cs_sigma_table.h"
 
 namespace cs {
@@ -133,36 +134,16 @@ __device__ __forceinline__ uint32_t shuffle_index(uint32_t i, uint32_t M, const 
 //   int w (2 - w) a^-2 dw = 2 phi2(z) / x^2 - phi3(z) / x^3,
 //     phi2 = log1p(z) - z / (1 + z),  phi3 = z - 2 log1p(z) + z / (1 + z),
 // and T = first + second - third.  With s = z / (2 + z) (so log1p(z) =
-// 2 atanh(s)) and q = s / x = v / (2 + z), sigma = s^2:
-//   log1p(z) / x = 2 q S1,            S1 = sum_{k>=0} sigma^k / (2k+1),
-//   phi2 / x^2 = q^2 (2 / (1 + s) + s S2),  S2 = sum_{k>=0} 2 sigma^k / (2k+3),
-//   phi3 / x^3 = q^3 S3,              S3 = sum_{k>=0} 8 (k+1) sigma^k / (2k+3).
-// Every term of the three series is positive, so they lose nothing to
-// cancellation at small x (where the closed form loses about 1/x^2 of its
-// precision); they converge like sigma^k with sigma < 1/4 for z < 2.  The
-// series branch serves x < 1; kTailTerms terms reach round-off at sigma
-// just below 1/4, and a lane with a smaller sigma takes fewer (see
-// tail_series).
-constexpr int kTailChunk = 6;   // terms per Horner chunk
-constexpr int kTailTerms = 30;  // five chunks
-constexpr double kSeriesSwitch = 1.0;
-
-struct TailCoeffs {
-    double s1[kTailTerms], s2[kTailTerms], s3[kTailTerms];
-};
-
-constexpr TailCoeffs tail_series_coeffs() {
-    TailCoeffs r{};
-    for (int k = 0; k < kTailTerms; ++k) {
-        const double kk = (double)k;
-        r.s1[k] = 1.0 / (2.0 * kk + 1.0);
-        r.s2[k] = 2.0 / (2.0 * kk + 3.0);
-        r.s3[k] = 8.0 * (kk + 1.0) / (2.0 * kk + 3.0);
-    }
-    return r;
-}
-
-__constant__ constexpr TailCoeffs kTail = tail_series_coeffs();
+// 2 atanh(s)), q = s / x = v / (2 + z) and sigma = s^2,
+//   log1p(z) = 2 s (1 + sigma P / 2),  P = sum_{k>=0} 2 sigma^k / (2k + 3),
+// and the powers of z cancel in closed form:
+//   T = v (2 + z) / (2 A^2) + q (2 - v (2 - v) / A) + q^3 (x^2 - 2x - 2) P.
+// One series of positive terms is all that is left of the logarithm (three
+// before, for the integrals one by one), nothing cancels by more than a factor
+// of two at any x, and the form holds down to x = 0.  It serves z < 2
+// (sigma < 1/4), with P the degree-15 polynomial of cs_icdf_table.h; above,
+// the logarithm itself is formed and the integrals are taken as they stand
+// (z >= 2 needs x >= 1, where they do not cancel).
 
 typedef const __attribute__((address_space(4))) double* cdptr;  // constant (scalar-load) space
 
@@ -175,91 +156,11 @@ __device__ __forceinline__ double fma_sgpr(double a, double b, double c) {
     return r;
 }
 
-// t^N by repeated squaring (N known at compile time).
-template <int N>
-__device__ __forceinline__ double ipow(double t) {
-    if constexpr (N == 1) {
-        return t;
-    } else if constexpr (N % 2 == 0) {
-        const double h = ipow<N / 2>(t);
-        return h * h;
-    } else {
-        return ipow<N - 1>(t) * t;
-    }
-}
-
 // 1/a to about an ulp (hardware estimate and two Newton steps).
 __device__ __forceinline__ double recip_approx(double a) {
     double r = __builtin_amdgcn_rcp(a);
     r = fma(fma(-a, r, 1.0), r, r);
     return fma(fma(-a, r, 1.0), r, r);
-}
-
-// sum_{k < 6 nch} c_k t^k for this lane's nch <= NC chunks of kTailChunk
-// terms: the wave evaluates NC chunks (Horner each, from scalar registers),
-// the lane zeroes those at or beyond its nch, and the chunks are combined
-// from the top in powers of t^6.  A zeroed chunk leaves the combination at
-// exactly 0 and fma(0, t^6, p) = p, so the lane's result is bit for bit its
-// own nch-chunk sum, whatever NC its wave needs.
-template <int NC>
-__device__ __forceinline__ double poly_lane_chunks(cdptr c, double t, int nch) {
-    double part[NC];
-#pragma unroll
-    for (int i = 0; i < NC; ++i) {
-        const int lo = i * kTailChunk;
-        double acc = c[lo + kTailChunk - 1];
-#pragma unroll
-        for (int k = lo + kTailChunk - 2; k >= lo; --k) acc = fma_sgpr(acc, t, c[k]);
-        part[i] = i == 0 || i < nch ? acc : 0.0;
-    }
-    if constexpr (NC == 1) {
-        return part[0];
-    } else {
-        const double tc = ipow<kTailChunk>(t);
-        double r = part[NC - 1];
-#pragma unroll
-        for (int i = NC - 2; i >= 0; --i) r = fma(r, tc, part[i]);
-        return r;
-    }
-}
-
-// T(v) from the three series, each with this lane's nch chunks (the wave's
-// NC >= nch evaluated).  The coefficient pointers pass through an empty asm
-// so that the compiler reads the coefficients with scalar loads at each use
-// instead of hoisting whole tables into vector registers across the
-// sampler's iteration.
-template <int NC>
-__device__ __forceinline__ double tail_terms(double v, double z, double A, double s, double q, double sig,
-                                             int nch) {
-    cdptr S1 = (cdptr)kTail.s1, S2 = (cdptr)kTail.s2, S3 = (cdptr)kTail.s3;
-    asm volatile("" : "+s"(S1), "+s"(S2), "+s"(S3));
-    const double p1 = poly_lane_chunks<NC>(S1, sig, nch);
-    const double p2 = poly_lane_chunks<NC>(S2, sig, nch);
-    const double p3 = poly_lane_chunks<NC>(S3, sig, nch);
-    const double iA = recip_approx(A);
-    const double first = 0.5 * v * (2.0 + z) * iA * iA;
-    const double inner = fma(s, p2, 2.0 * recip_approx(1.0 + s));
-    return first + 2.0 * q * p1 - 2.0 * q * q * inner + q * q * q * p3;
-}
-
-// Series branch of T(v) for x < kSeriesSwitch.  Each lane takes as many
-// terms as its own sigma needs for the truncated remainder to stay below
-// 1e-17 of the sum: 6 terms up to sigma = 1.5e-3, 12 up to 0.035, 18 up to
-// 0.112, else kTailTerms (sigma < 1/4).  The wave evaluates the chunks its
-// largest need requires; a lane's result depends on its own sigma only
-// (poly_lane_chunks), so it is the same whichever lanes share its wave --
-// every kernel strategy, whose waves group the collisions differently,
-// gives the same bits.
-__device__ __forceinline__ double tail_series(double x, double v) {
-    const double z = x * v;
-    const double r = recip_approx(2.0 + z);
-    const double s = z * r, q = v * r, sig = s * s;
-    const double A = 1.0 + z;
-    const int nch = sig <= 1.5e-3 ? 1 : (sig <= 0.035 ? 2 : (sig <= 0.112 ? 3 : kTailTerms / kTailChunk));
-    if (__all(nch <= 1)) return tail_terms<1>(v, z, A, s, q, sig, nch);
-    if (__all(nch <= 2)) return tail_terms<2>(v, z, A, s, q, sig, nch);
-    if (__all(nch <= 3)) return tail_terms<3>(v, z, A, s, q, sig, nch);
-    return tail_terms<kTailTerms / kTailChunk>(v, z, A, s, q, sig, nch);
 }
 
 // s(x) = sigma_KN(x) / sigma_T.  Below 2: the per-segment Taylor polynomial
@@ -297,95 +198,256 @@ __device__ __forceinline__ double sigma_ratio_tab(double x, const double* tab) {
 
 __device__ __forceinline__ double sigma_ratio(double x) { return sigma_ratio_tab(x, kSigTab); }
 
-// Unnormalised angular density f at mu = 1 - v, for x >= 0.
-__device__ __forceinline__ double angle_density_v(double v, double x) {
-    const double a = 1.0 + x * v;
-    const double ia = 1.0 / a;
-    return ia * ia * ia + ia - v * (2.0 - v) * ia * ia;
+// Whether p holds in an active lane (a scalar test of the compare's mask).
+__device__ __forceinline__ bool any_lane(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
+
+// P(sigma) for 0 <= sigma < 1/4.  sigma <= 1.5e-3: the first six terms of
+// the series (remainder below 1e-17), else the degree-15 polynomial in two
+// interleaved Horner chains.  Which form a lane takes depends on its own
+// sigma only, so its bits do not depend on the lanes that share its wave; a
+// wave whose lanes are all small skips the longer form.  The coefficient
+// pointer passes through an empty asm so that the coefficients are read with
+// scalar loads at each use instead of being held in vector registers.
+__device__ __forceinline__ double tail_poly(double sg) {
+    const bool low = sg <= 1.5e-3;
+    double p = 2.0 / 3.0;
+    if (any_lane(low)) {
+        double t = 2.0 / 13.0;
+        t = fma_sgpr(t, sg, 2.0 / 11.0);
+        t = fma_sgpr(t, sg, 2.0 / 9.0);
+        t = fma_sgpr(t, sg, 2.0 / 7.0);
+        t = fma_sgpr(t, sg, 2.0 / 5.0);
+        p = fma_sgpr(t, sg, 2.0 / 3.0);
+    }
+    if (any_lane(!low)) {
+        cdptr c = (cdptr)kTailPoly;
+        asm volatile("" : "+s"(c));
+        static_assert(kTailPolyTerms % 2 == 0, "two chains of equal length");
+        const double s2 = sg * sg;
+        double e = c[kTailPolyTerms - 2], o = c[kTailPolyTerms - 1];
+#pragma unroll
+        for (int k = kTailPolyTerms - 4; k >= 0; k -= 2) {
+            e = fma_sgpr(e, s2, c[k]);
+            o = fma_sgpr(o, s2, c[k + 1]);
+        }
+        const double h = fma(o, sg, e);
+        if (!low) p = h;
+    }
+    return p;
 }
 
+// T(v) at x, with what the density at v needs besides: iA = 1 / (1 + x v)
+// and w = v (2 - v).  One reciprocal serves 1/A and the argument of the
+// series: for z < 2 of s = z / (2 + z), above of (m - 1) / (m + 1) with
+// A = 2^k m, m in [1/sqrt 2, sqrt 2), whose logarithm takes the same P.
+// ANY_BIG = false: for waves without a lane of z >= 2 (the same arithmetic
+// for the others).
+struct KnTail {
+    double T, iA, w;
+};
 
-// int_{1 - v}^{1} f dmu (upper tail), for 0 <= v <= 2.
-//   series branch (x < kSeriesSwitch): as above;
-//   closed branch: with a = 1 + x v and G' = f in a,
-//   (1/x)[G(a) - G(1)] = (1/x)[ x v (2 + x v) / (2 a^2) + log1p(x v)
-//                        - (-(x v) + (2x+2) log1p(x v) - (2x+1) x v / a) / x^2 ].
-__device__ __forceinline__ double angle_tail(double v, double x) {
-    if (x < kSeriesSwitch) return tail_series(x, v);
-    const double xv = x * v;
-    const double a = 1.0 + xv;
-    const double L = log1p(xv);
-    const double g = xv * (2.0 + xv) / (2.0 * a * a) + L -
-                     (-xv + (2.0 * x + 2.0) * L - (2.0 * x + 1.0) * xv / a) / (x * x);
-    return g / x;
+template <bool ANY_BIG>
+__device__ __forceinline__ KnTail kn_tail_z(double v, double x, double z, bool big) {
+    const double t2 = z + 2.0, A = z + 1.0;
+    double num = z, den = t2, k = 0.0;
+    if (ANY_BIG && big) {
+        const double m0 = __builtin_amdgcn_frexp_mant(A);  // [1/2, 1)
+        const bool low = m0 < 0.70710678118654757;
+        const double m = low ? m0 + m0 : m0;
+        k = (double)(__builtin_amdgcn_frexp_exp(A) - (low ? 1 : 0));
+        num = m - 1.0;
+        den = m + 1.0;
+    }
+    // one hardware estimate for both reciprocals, the last Newton step on each
+    const double dA = den * A;
+    double rr = __builtin_amdgcn_rcp(dA);
+    rr = fma(fma(-dA, rr, 1.0), rr, rr);
+    const double r0 = rr * A, i0 = rr * den;
+    const double r = fma(fma(-den, r0, 1.0), r0, r0);
+    KnTail o;
+    o.iA = fma(fma(-A, i0, 1.0), i0, i0);
+    o.w = fma(-v, v, v + v);
+    const double s = num * r, sg = s * s;
+    const double P = tail_poly(sg);
+    const double first = 0.5 * v * (t2 * o.iA) * o.iA;
+    if (!(ANY_BIG && big)) {
+        const double q = v * r;
+        const double c = fma(x, x - 2.0, -2.0);
+        o.T = fma(q, fma(-o.w, o.iA, 2.0), fma(q * q * q, P * c, first));
+    } else {
+        // ln A = k ln 2 + 2 atanh(s); ln 2 as its leading 32 bits and the rest
+        const double l = s * fma(sg, P, 2.0);
+        const double lnA = fma(k, 0x1.62e42feep-1, fma(k, 0x1.a39ef35793c76p-33, l));
+        const double ix = recip_approx(x), zA = z * o.iA;
+        const double phi2 = lnA - zA, phi3 = (z - 2.0 * lnA) + zA;
+        o.T = first + ix * (lnA - ix * (2.0 * phi2 - phi3 * ix));
+    }
+    return o;
 }
 
-// Thomson-limit inverse (x -> 0): root of (mu^3 + 3 mu + 4)/8 = u by Cardano;
-// with q = 4u - 2 and A = cbrt(q + sqrt(q^2 + 1)) the root is A - 1/A.
-__device__ __forceinline__ double thomson_root(double u) {
-    const double q = 4.0 * u - 2.0;
-    const double A = cbrt(q + sqrt(q * q + 1.0));
-    return A - 1.0 / A;
+__device__ __forceinline__ KnTail kn_tail(double v, double x) {
+    const double z = x * v;
+    const bool big = z >= 2.0;
+    if (any_lane(big)) return kn_tail_z<true>(v, x, z, big);
+    return kn_tail_z<false>(v, x, z, false);
+}
+
+// (8/3) s(x) = T(2): the whole angular integral.
+__device__ __forceinline__ double kn_total(double x) {
+    if (x < kSmallX) {
+        double z = kSmallZ[kSmallZTerms - 1];
+#pragma unroll
+        for (int k = kSmallZTerms - 2; k >= 0; --k) z = fma_sgpr(z, x, kSmallZ[k]);
+        return z;
+    }
+    return kn_tail(2.0, x).T;
+}
+
+// FP32 Horner chain with compile-time coefficients, degree D.
+template <int D>
+__device__ __forceinline__ float horner_f32(const float (&c)[D + 1], float t) {
+    float a = c[D];
+#pragma unroll
+    for (int k = D - 1; k >= 0; --k) a = fmaf(a, t, c[k]);
+    return a;
+}
+
+// Row j of the starting value's polynomial at w.
+template <int J>
+__device__ __forceinline__ float start_row(float w) {
+    float a = kStart[J][kStartDeg[J]];
+#pragma unroll
+    for (int k = kStartDeg[J] - 1; k >= 0; --k) a = fmaf(a, w, kStart[J][k]);
+    return a;
+}
+
+// The root v of T(v) = target to about 1e-6 in FP32, for kSmallX <= x: the
+// polynomial starting value (1e-2), then one Halley step on the FP32 tail.
+__device__ __forceinline__ float icdf_start(float w, float x, float target) {
+    const float lx = x < 0.03f ? fmaf(x, fmaf(x, 2.6666667f, -2.0f), 2.0f)
+                               : 0.69314718f * __builtin_amdgcn_logf(fmaf(2.0f, x, 1.0f)) * __builtin_amdgcn_rcpf(x);
+    const float L = lx * x;  // ln(1 + 2x)
+    const float t = L * __builtin_amdgcn_rcpf(L + kStartShift);
+    static_assert(kStartRows == 5, "rows");
+    float h = start_row<4>(w);
+    h = fmaf(h, t, start_row<3>(w));
+    h = fmaf(h, t, start_row<2>(w));
+    h = fmaf(h, t, start_row<1>(w));
+    h = fmaf(h, t, start_row<0>(w));
+    h *= w;
+    const float y = h * L;  // ln(1 + x v); v = (e^y - 1) / x
+    float v = y < 0.25f ? h * lx * fmaf(y, fmaf(y, fmaf(y, 0.041666668f, 0.16666667f), 0.5f), 1.0f)
+                        : (__builtin_amdgcn_exp2f(1.44269504f * y) - 1.0f) * __builtin_amdgcn_rcpf(x);
+    v = fminf(v, 2.0f);
+    const float z = x * v, t2 = z + 2.0f, A = z + 1.0f;
+    const float rr = __builtin_amdgcn_rcpf(t2 * A);
+    const float r = rr * A, iA = rr * t2;
+    const float wv = fmaf(-v, v, v + v);
+    const float first = 0.5f * v * (t2 * iA) * iA;
+    float T;
+    if (z < 2.0f) {
+        const float s = z * r, sg = s * s, q = v * r;
+        const float P = horner_f32<kStartTailDeg>(kStartTail, sg);
+        T = first + q * fmaf(-wv, iA, 2.0f) + (q * q * q) * (P * fmaf(x, x - 2.0f, -2.0f));
+    } else {
+        const float lnA = 0.69314718f * __builtin_amdgcn_logf(A);
+        const float ix = __builtin_amdgcn_rcpf(x), zA = z * iA;
+        T = first + ix * (lnA - ix * (2.0f * (lnA - zA) - ((z - 2.0f * lnA) + zA) * ix));
+    }
+    const float R = T - target;
+    const float f = iA * fmaf(iA, iA - wv, 1.0f);
+    const float g = fmaf(x, fmaf(iA, fmaf(3.0f, iA, -2.0f * wv), 1.0f), 2.0f - 2.0f * v);  // f' = -iA^2 g
+    return v - 2.0f * R * f * __builtin_amdgcn_rcpf(fmaf(R * iA * iA, g, 2.0f * f * f));
+}
+
+// The same for x < kSmallX: starting value w (A(w) + x B(w)) (6e-4), then a
+// Newton step on the tail and its density as polynomials to second order in x.
+__device__ __forceinline__ float icdf_start_small(float w, float x, float target) {
+    float v = w * fmaf(x, horner_f32<kStartSmallB>(kStartB, w), horner_f32<kStartSmallA>(kStartA, w));
+    v = fminf(v, 2.0f);
+    const float wv = fmaf(-v, v, v + v);
+    const float xv = x * v;
+    const float t0 = fmaf(v, fmaf(v, 0.33333333f, -1.0f), 2.0f);
+    const float t1 = fmaf(v, fmaf(v, -0.5f, 1.3333333f), -2.0f);
+    const float tq = fmaf(v, fmaf(v, 0.6f, -1.5f), 2.3333333f);
+    const float R = fmaf(v, fmaf(xv, fmaf(xv, tq, t1), t0), -target);
+    const float f = fmaf(xv, fmaf(2.0f, wv, -4.0f), 2.0f - wv);
+    return fmaf(-R, __builtin_amdgcn_rcpf(f), v);
+}
+
+// One step of third order in FP64 from v towards the root of T(v) = target:
+// d = R / f (R the residual, f the density), v - d (1 + d f' / (2 f)).
+struct IcdfStep {
+    double R, d, c2;  // residual, Newton step, d f' / (2 f)
+};
+
+__device__ __forceinline__ IcdfStep icdf_step(double v, double x, double target) {
+    const KnTail t = kn_tail(v, x);
+    const double a2 = t.iA * t.iA;
+    const double h = fma(-t.iA, t.w, 1.0 + a2);
+    const double f = t.iA * h;
+    double rf = __builtin_amdgcn_rcp(f);
+    rf = fma(fma(-f, rf, 1.0), rf, rf);
+    IcdfStep s;
+    s.R = t.T - target;
+    s.d = s.R * rf;
+    // f' = -iA^2 (2 - 2v + x (1 + iA (3 iA - 2 w)))
+    const double g = fma(x, fma(2.0, h, a2 - 1.0), fma(-2.0, v, 2.0));
+    s.c2 = (-0.5 * s.d) * (a2 * (g * rf));
+    return s;
+}
+
+// More steps where one did not settle it (a start far off: x beyond the
+// fitted range), safeguarded by a bisection bracket.
+__device__ __attribute__((noinline)) double icdf_refine(double v, double x, double target) {
+    double lo = 0.0, hi = 2.0;
+    for (int it = 0; it < 60; ++it) {
+        const IcdfStep s = icdf_step(v, x, target);
+        double next = v - fma(s.d, fabs(s.c2) < 0.5 ? s.c2 : 0.0, s.d);
+        if (fabs(s.d) <= 3e-6 * v) return next;
+        if (s.R > 0.0)  // v too large
+            hi = v;
+        else
+            lo = v;
+        if (!(next > lo && next < hi)) next = 0.5 * (lo + hi);
+        v = next;
+        if (hi - lo <= 1e-16 * hi) break;
+    }
+    return v;
 }
 
 // Inverse CDF of the rest-frame scattering angle, returned as v = 1 - mu so
 // that forward scatters (mu -> 1) keep relative precision: the v with
 // tail(v) = (1 - u) Z, Z = tail(2) = (8/3) s(x).
 //
-// Start: for x < 1/2 the Thomson root v0 = 1 - mu0 corrected to first order
-// in x: with tail = v(2 - v + v^2/3) - x v^2 (2 - 4v/3 + v^2/2) + O(x^2) and
-// Z = 8/3 - 16x/3 + O(x^2), v1 = [v0^2 (2 - 4 v0/3 + v0^2/2) - 16(1 - u)/3]
-// / (2 - 2 v0 + v0^2); for x >= 1/2 the inverse of the large-x law
-// F ~ ln((1+2x)/a) / ln(1+2x), a = 1 + x v.  Then Halley's iteration in v
-// (slope: the density f; curvature: f' in closed form), safeguarded by a
-// bisection bracket, falling back to a Newton step if Halley's denominator
-// is not positive.  A Halley step below 1e-5 v (a Newton step below 1e-8 v)
-// is accepted and ends the iteration: the error after it is at round-off
-// (cubic convergence leaves about C v (1e-5)^3, quadratic C v (1e-8)^2, with
-// C = O(1); against the converged root the accepted values stay within
-// 2.2e-15 relative over x in [1e-4, 1e3]).  An exact zero residual ends it
-// too.  Only the residual (the tail series or closed
-// form) decides where the iteration lands, so the step sizes use reciprocal
-// estimates refined to about an ulp.
+// An FP32 start good to about 1e-6 (icdf_start: a fitted polynomial and one
+// Halley step), then one step of third order on the FP64 residual.  A step
+// below 3e-6 v ends the iteration, the error after it being about
+// C v (3e-6)^3, C = O(1): round-off, which only the FP64 residual decides.
+//
+// What bounds it: VALU issue, about four cycles per wave and instruction in
+// FP32 and FP64 alike, so the number of instructions counts, whatever their
+// type: 397 per wave with x over [1e-8, 1e3] in every wave, 138 where all
+// are below kSmallX.  k_sample_plain on 2^22 FP32 samples of the former:
+// 176.4 us with three series up to 30 terms for the tail below x = 1, its
+// closed form above, and 2-4 FP64 Halley steps from the Thomson root;
+// 42.8 us with this (22.6 us for the power-law plasma's inputs, 50.2 before).
+// The two starts part at kSmallX because the cheap one needs the tail's
+// expansion in x; the whole grid range on icdf_start alone would slow the
+// small-x plasmas to its cost.
 __device__ __forceinline__ double angle_icdf_v(double u, double x) {
-    const double Z = (8.0 / 3.0) * sigma_ratio(x);
-    const double target = (1.0 - u) * Z;  // 1 - u is exact for u = k 2^-53
-    double lo = 0.0, hi = 2.0;
-    double v;
-    if (x < 0.5) {
-        const double v0 = 1.0 - thomson_root(u);
-        const double v1 = (v0 * v0 * (2.0 - 4.0 / 3.0 * v0 + 0.5 * v0 * v0) - 16.0 / 3.0 * (1.0 - u)) /
-                          (2.0 - 2.0 * v0 + v0 * v0);
-        v = v0 + x * v1;
-    } else {
-        v = expm1((1.0 - u) * log1p(2.0 * x)) / x;
+    const double w1 = 1.0 - u;  // exact for u = k 2^-53
+    const double target = w1 * kn_total(x);
+    const float start = x < kSmallX ? icdf_start_small((float)w1, (float)x, (float)target)
+                                    : icdf_start((float)w1, (float)x, (float)target);
+    const double v = (double)__builtin_amdgcn_fmed3f(start, 0.0f, 2.0f);
+    const IcdfStep s = icdf_step(v, x, target);
+    double next = v - fma(s.d, s.c2, s.d);
+    const bool settled = fabs(s.d) <= 3e-6 * v;
+    if (any_lane(!settled)) {
+        if (!settled) next = icdf_refine(v, x, target);
     }
-    v = fmin(fmax(v, 0.0), 2.0);
-    for (int it = 0; it < 60; ++it) {
-        const double R = angle_tail(v, x) - target;  // > 0: v too large
-        if (R == 0.0) break;
-        if (R > 0.0)
-            hi = v;
-        else
-            lo = v;
-        // Halley step on the tail: slope f (the density) and curvature f'
-        const double ia = recip_approx(1.0 + x * v);
-        const double ia2 = ia * ia, ia3 = ia2 * ia;
-        const double w = v * (2.0 - v);
-        const double f = ia3 + ia - w * ia2;
-        const double fp = -3.0 * x * ia3 * ia - x * ia2 - (2.0 - 2.0 * v) * ia2 + 2.0 * x * w * ia3;
-        const double den = 2.0 * f * f - R * fp;
-        const bool halley = den > 0.0;
-        double next = halley ? v - 2.0 * R * f * recip_approx(den) : v - R * recip_approx(f);
-        if (fabs(next - v) <= (halley ? 1e-5 : 1e-8) * next) {
-            v = next;
-            break;
-        }
-        if (!(next > lo && next < hi)) next = 0.5 * (lo + hi);
-        v = next;
-        if (hi - lo <= 1e-16 * hi) break;
-    }
-    return fmin(fmax(v, 0.0), 2.0);
+    return fmin(next, 2.0);
 }
 
 // ---------------------------------------------------------------------------

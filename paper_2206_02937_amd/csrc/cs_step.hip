@@ -360,14 +360,32 @@ __global__ __launch_bounds__(256) void k_finalize(const int32_t* __restrict__ fl
     }
 }
 
+// The plain sampler on its own.  A workgroup takes the 256-sample pieces
+// blockIdx, blockIdx + gridDim, ... and reads the next one's inputs before
+// it works on the present one; a piece's addresses are scalar.
 template <typename T>
 __global__ __launch_bounds__(256) void k_sample_plain(const T* __restrict__ x, const T* __restrict__ u, int64_t n,
                                                       T* __restrict__ mu_out, T* __restrict__ ratio_out) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const double xi = (double)x[i];
-        const double v = angle_icdf_v((double)u[i], xi);
-        mu_out[i] = (T)(1.0 - v);
-        ratio_out[i] = (T)(1.0 / (1.0 + xi * v));
+    const uint32_t tid = threadIdx.x;
+    const int64_t n_pieces = (n + 255) / 256;
+    int64_t piece = blockIdx.x;
+    // (the last piece's missing samples read its first one)
+    auto lane_of = [&](int64_t p) { return (int64_t)tid < n - p * 256 ? tid : 0u; };
+    T xn = (x + piece * 256)[lane_of(piece)], un = (u + piece * 256)[lane_of(piece)];
+    for (; piece < n_pieces; piece += gridDim.x) {
+        const T xc = xn, uc = un;
+        const int64_t next = piece + gridDim.x < n_pieces ? piece + gridDim.x : piece;
+        xn = (x + next * 256)[lane_of(next)];
+        un = (u + next * 256)[lane_of(next)];
+        const double xi = (double)xc;
+        const double v = angle_icdf_v((double)uc, xi);
+        const double a = fma(xi, v, 1.0);
+        if ((int64_t)tid < n - piece * 256) {
+            // (streamed out as they come, not left for the end-of-kernel write-back)
+            __builtin_nontemporal_store((T)(1.0 - v), &(mu_out + piece * 256)[tid]);
+            __builtin_nontemporal_store((T)(sizeof(T) == 4 ? recip_approx(a) : 1.0 / a),
+                                        &(ratio_out + piece * 256)[tid]);
+        }
     }
 }
 
@@ -482,7 +500,7 @@ hipError_t launch_sample_plain(cs_dtype dtype, const void* x, const void* u, int
                                hipStream_t st) {
     if (n <= 0) return hipSuccess;
     const int64_t nb = (n + 255) / 256;
-    const unsigned grid = (unsigned)(nb < 65536 ? nb : 65536);
+    const unsigned grid = (unsigned)(nb < 2048 ? nb : 2048);
     if (dtype == CS_F64)
         k_sample_plain<double><<<grid, 256, 0, st>>>((const double*)x, (const double*)u, n, (double*)mu,
                                                      (double*)ratio);
