@@ -305,8 +305,8 @@ CS_API cs_status cs_pnet_forward(cs_ctx* ctx, const float* params, const float* 
  * mean |y' - t|, mean (y' - t)^2 / 2) with respect to the parameters into
  * grad_out (CS_PNET_PARAMS), and the loss into *loss_out (device scalar, may
  * be NULL).  Per-pair contributions are summed in a fixed order (the result
- * does not depend on timing).  The context keeps a scratch of about 1.3 n
- * bytes, grown on demand (a growth synchronises `stream`). */
+ * does not depend on timing).  The context keeps a scratch of about 5.3 n
+ * bytes up to 1.4 MB, grown on demand (a growth synchronises `stream`). */
 CS_API cs_status cs_pnet_grad(cs_ctx* ctx, const float* params, const float* in, const float* target, int64_t n,
                        cs_loss loss, float* grad_out, float* loss_out, void* stream);
 

@@ -141,3 +141,22 @@ def test_training_driver_stages_and_export(ctx):
     y_raw = ctx.pnet_forward(_dev(params), _dev(X)).cpu().numpy()
     y_scaled = ctx.pnet_forward(_dev(scaled), _dev(X / T.SCALE)).cpu().numpy()
     assert np.max(np.abs(y_raw - y_scaled)) <= 1e-5
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 257, 1024 * 256 - 1, 1024 * 256 + 65])
+def test_grad_at_tile_and_grid_edges(ctx, n):
+    """Waves, workgroups and the grid's second round partly filled, against the
+    oracle.  Tolerance: FP32 forward and backward (as for the ragged batch
+    above), relative to the largest sum of absolute contributions, which bounds
+    what rounding can leave of a cancelling sum."""
+    rng = np.random.default_rng(n)
+    params = (N.glorot_uniform(rng) + rng.normal(0, 0.05, N.n_params())).astype(np.float32)
+    X = (_pairs(rng, n) * np.array([1, 1, 1, 0.1, 0.1, 0.1, 1, 1, 1])).astype(np.float32)
+    t = rng.uniform(0, 1, n).astype(np.float32)
+    g, l = ctx.pnet_grad(_dev(params), _dev(X), _dev(t), "mse")
+    p64, X64, t64 = params.astype(np.float64), X.astype(np.float64), t.astype(np.float64)
+    g_ref, l_ref = N.grad(p64, X64, t64, "mse")
+    y = N.forward(p64, X64)
+    scale = max(np.max(np.abs(g_ref)), float(np.mean(np.abs(y - t64) * y * (1 - y))))
+    assert np.max(np.abs(g.cpu().numpy().astype(np.float64) - g_ref)) <= 2e-5 * scale
+    assert float(l.cpu().numpy()[0]) == pytest.approx(l_ref, rel=1e-5)
