@@ -672,128 +672,20 @@ __global__ __launch_bounds__(kMfmaThreads, kMfmaWavesPerSimd) void k_mlp_mfma(co
 }
 
 // ---------------------------------------------------------------------------
-// FP32 inference on MFMA (v_mfma_f32_16x16x4_f32)
+// FP32 inference on MFMA (mlp_tiles_f32)
 // ---------------------------------------------------------------------------
-// The layout of the reduced-precision engine (lane l owns sample l % 16 and
-// neurons 16t + 4g + r of a 16-sample tile, g = l / 16), with the K index of
-// each layer's contraction permuted so that every lane's B operand is one of
-// its own outputs of the previous layer: k-step (t, r) pairs lane group g
-// with input neuron 16t + 4g + r, so the A operand of lane l at (output tile
-// T, k-step (t, r)) is W[16T + l % 16][16t + 4 (l / 16) + r].  These
-// fragments (3 layers x 4 x 16 x 64 floats, 48 KB) are built in LDS by each
-// workgroup.  SiLU is the correctly rounded FP32 one; the first and last
-// layers run on the vector ALUs as in the other engine.
-constexpr int kF32Frag = 3 * 4 * 16 * 64;
-
-struct F32Lds {
-    float frag[kF32Frag];
-    float P[kSmall];  // W1, b1..b4, W5, b5 (unscaled)
-};
-
-__device__ __forceinline__ void f32_lds_load(F32Lds& s, const float* P) {
-    const int offW[3] = {kOffW2, kOffW3, kOffW4};
-    for (int i = threadIdx.x; i < kF32Frag; i += blockDim.x) {
-        const int l = i & 63, rr = (i >> 6) & 3, t = (i >> 8) & 3, T = (i >> 10) & 3, L = i >> 12;
-        s.frag[i] = P[offW[L] + (16 * T + (l & 15)) * kMlpHidden + 16 * t + 4 * (l >> 4) + rr];
-    }
-    for (int i = threadIdx.x; i < kSmall; i += blockDim.x) {
-        int src;
-        if (i < cB1)
-            src = kOffW1 + i;
-        else if (i < cB2)
-            src = kOffB1 + (i - cB1);
-        else if (i < cB3)
-            src = kOffB2 + (i - cB2);
-        else if (i < cB4)
-            src = kOffB3 + (i - cB3);
-        else if (i < cW5)
-            src = kOffB4 + (i - cB4);
-        else if (i < cB5)
-            src = kOffW5 + (i - cW5);
-        else
-            src = kOffB5 + (i - cB5);
-        s.P[i] = P[src];
-    }
-}
-
-// NTL tiles side by side; amax (nullable): this lane's running max |h| of the
-// inputs of hidden layers 2..4, over the tiles k whose sample is real[k].
-template <int NTL>
-__device__ __forceinline__ void mlp_tiles_f32(const float* frag, const float* Ps, const float (&f1)[NTL],
-                                              const float (&f2)[NTL], float (&y0)[NTL], float (&y1)[NTL],
-                                              float* amax, const bool (&real)[NTL]) {
-    const int lane = lane_id();
-    const int g = lane >> 4;
-    float h[NTL][16];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int n = 16 * t + 4 * g + r;
-            const float w1a = Ps[cW1 + 2 * n], w1b = Ps[cW1 + 2 * n + 1], b1 = Ps[cB1 + n];
-#pragma unroll
-            for (int k = 0; k < NTL; ++k) {
-                h[k][4 * t + r] = silu_f32(fmaf(w1b, f2[k], fmaf(w1a, f1[k], b1)));
-                if (amax && real[k]) amax[0] = fmaxf(amax[0], fabsf(h[k][4 * t + r]));
-            }
-        }
-    const int offB[3] = {cB2, cB3, cB4};
-#pragma unroll
-    for (int L = 0; L < 3; ++L) {
-        float o[NTL][16];
-#pragma unroll
-        for (int T = 0; T < 4; ++T) {
-            floatx4 acc[NTL];
-#pragma unroll
-            for (int k = 0; k < NTL; ++k)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[k][r] = Ps[offB[L] + 16 * T + 4 * g + r];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const float A = frag[((L * 4 + T) * 16 + q) * 64 + lane];
-#pragma unroll
-                for (int k = 0; k < NTL; ++k) acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(A, h[k][q], acc[k], 0, 0, 0);
-            }
-#pragma unroll
-            for (int k = 0; k < NTL; ++k)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) o[k][4 * T + r] = silu_f32(acc[k][r]);
-        }
-#pragma unroll
-        for (int k = 0; k < NTL; ++k)
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                h[k][j] = o[k][j];
-                if (amax && L < 2 && real[k]) amax[L + 1] = fmaxf(amax[L + 1], fabsf(o[k][j]));
-            }
-    }
-#pragma unroll
-    for (int k = 0; k < NTL; ++k) {
-        float p0 = 0.0f, p1 = 0.0f;
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int n = 16 * t + 4 * g + r;
-                p0 = fmaf(Ps[cW5 + n], h[k][4 * t + r], p0);
-                p1 = fmaf(Ps[cW5 + kMlpHidden + n], h[k][4 * t + r], p1);
-            }
-        p0 += __shfl_xor(p0, 16, 64);
-        p1 += __shfl_xor(p1, 16, 64);
-        p0 += __shfl_xor(p0, 32, 64);
-        p1 += __shfl_xor(p1, 32, 64);
-        y0[k] = p0 + Ps[cB5];
-        y1[k] = p1 + Ps[cB5 + 1];
-    }
-}
-
 // FP32 forward / sampler / calibration: the walk of k_mlp_mfma (64-sample
 // groups per wave, the out-of-domain samples in a second walk), two tiles
 // side by side.
+template <bool CALIB>
 __global__ __launch_bounds__(kMfmaThreads, 2) void k_mlp_f32(const FwdArgs a) {
-    __shared__ F32Lds s_net;
+    __shared__ NetLds<CS_SAMPLER_MLP_F32> s_net;
     __shared__ int64_t s_fb[kMfmaThreads / 64][kFbCap];
-    f32_lds_load(s_net, a.P);
+    {
+        MlpDev m = {};
+        m.params = a.P;
+        net_load<CS_SAMPLER_MLP_F32>(s_net, m);
+    }
     __syncthreads();
     const int lane = lane_id();
     const int wave = wave_uniform((int)threadIdx.x >> 6);
@@ -810,7 +702,7 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_mlp_f32(const FwdArgs a) {
         features(x, u, a.dom, f1, f2);
         int opaque = 0;
         asm volatile("" : "+s"(opaque));
-        const float* frag = s_net.frag + opaque;
+        const float4* frag = s_net.frag + opaque;
         const float* Ps = s_net.P + opaque;
         float o0 = 0.0f, o1 = 0.0f;
 #pragma unroll
@@ -826,7 +718,7 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_mlp_f32(const FwdArgs a) {
             // of tile t0 + k evaluates sample 16 (t0 + k) + li of the group
             const bool real[2] = {grp * 64 + 16 * t0 + (lane & 15) < a.n,
                                   grp * 64 + 16 * (t0 + 1) + (lane & 15) < a.n};
-            mlp_tiles_f32<2>(frag, Ps, g1, g2, y0, y1, a.amax ? amax : nullptr, real);
+            mlp_tiles_f32<2, CALIB>(frag, Ps, g1, g2, y0, y1, CALIB ? amax : nullptr, real);
 #pragma unroll
             for (int k = 0; k < 2; ++k)
                 if ((lane >> 4) == t0 + k) {
@@ -837,7 +729,7 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_mlp_f32(const FwdArgs a) {
         if (active && a.y) *(float2*)(a.y + 2 * i) = make_float2(o0, o1);
         if (sampling && active && in_range(x, a.dom)) net_out(a, i, x, o0, o1);
     }
-    if (a.amax) {
+    if constexpr (CALIB) {
         // non-negative floats order as their bits
 #pragma unroll
         for (int L = 0; L < 3; ++L) {
@@ -903,7 +795,7 @@ hipError_t launch_mlp_forward(const MlpDev& m, cs_sampler prec, const float* x, 
         const int64_t groups = (n + 63) / 64;
         int64_t blocks = (groups + kMfmaThreads / 64 - 1) / (kMfmaThreads / 64);
         if (blocks > 1024) blocks = 1024;
-        k_mlp_f32<<<(unsigned)blocks, kMfmaThreads, 0, st>>>(a);
+        k_mlp_f32<false><<<(unsigned)blocks, kMfmaThreads, 0, st>>>(a);
     } else {
         // one 64-sample group per wave and step of the loop; 2048 workgroups
         // (8 per compute unit) cover the chip
@@ -961,7 +853,7 @@ hipError_t launch_mlp_quantize(float* params, const NetDomain& dom, void* frag_b
         const int64_t groups = (n + 63) / 64;
         int64_t blocks = (groups + kMfmaThreads / 64 - 1) / (kMfmaThreads / 64);
         if (blocks > 1024) blocks = 1024;
-        k_mlp_f32<<<(unsigned)blocks, kMfmaThreads, 0, st>>>(a);
+        k_mlp_f32<true><<<(unsigned)blocks, kMfmaThreads, 0, st>>>(a);
         k_mlp_act_scale<<<1, 64, 0, st>>>(scales);
         k_mlp_weight_scale<<<3, 256, 0, st>>>(params, scales);
         k_mlp_build_frag<<<nb, 256, 0, st>>>(params, scales, CS_SAMPLER_MLP_FP8, nullptr, (uint8_t*)frag_fp8);

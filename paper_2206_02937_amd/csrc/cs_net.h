@@ -7,10 +7,8 @@
 // cos(theta), output 1 the energy ratio.
 //
 // Two evaluators:
-//   * FP32: either a workgroup-wide engine (cs_mlp.hip) or, inside the step,
-//     one lane per sample (mlp_lane_f32) with the layer outputs in LDS.  Both
-//     accumulate b + sum_k W[j][k] h[k] with k ascending and fmaf, so they
-//     agree bitwise.
+//   * FP32 (mlp_tiles_f32): the same walk on v_mfma_f32_16x16x4_f32, with the
+//     FP32 weight fragments in LDS.
 //   * MFMA (BF16 / FP8 E4M3): a wave evaluates 16 samples per tile with
 //     v_mfma_f32_16x16x32_{bf16,fp8}.  Lane l owns sample l%16 and, in group
 //     g = l/16, the neurons 16t + 4g + r (t, r = 0..3): exactly the rows of
@@ -36,6 +34,24 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr float kE4M3Max = 448.0f;
 
 __device__ __forceinline__ float silu_f32(float z) { return z / (1.0f + expf(-z)); }
+
+// The same for FP32 inference, in half the instructions: e^-z from the
+// hardware exp2 with the rounding of its argument compensated (within 1.5
+// ulp), and the quotient from the reciprocal estimate and one residual
+// correction (correctly rounded but for near-ties).  -z is capped at 87,
+// where SiLU is below 1e-36, so that the denominator stays finite (a NaN
+// passes through the quotient).
+__device__ __forceinline__ float silu_f32_fast(float z) {
+    const float y = __builtin_amdgcn_fmed3f(-z, -126.0f, 87.0f);
+    const float t = y * 1.44269504f;
+    // y log2(e) - t: the product's rounding and log2(e)'s
+    const float d = fmaf(y, 1.92596299e-8f, fmaf(y, 1.44269504f, -t));
+    const float ex = __builtin_amdgcn_exp2f(t);
+    const float den = 1.0f + fmaf(ex, 0.69314718f * d, ex);
+    const float r = __builtin_amdgcn_rcpf(den);
+    const float q = z * r;
+    return fmaf(fmaf(-den, q, z), r, q);
+}
 
 // The reduced-precision paths carry every pre-activation and activation of
 // the hidden layers scaled by kSiluScale = -log2(e): with t = kSiluScale z,
@@ -273,42 +289,117 @@ __device__ __forceinline__ void mlp_tile(const typename FragT<PREC>::type* frag,
     y1 = b1[0];
 }
 
-// One sample per lane in FP32, both outputs.  hb: this wave's [64 neurons]
-// [64 lanes] LDS buffer.  The weights are read with wave-uniform addresses
-// (scalar loads).  Must be called by the whole wave.
-__device__ __forceinline__ float2 mlp_lane_f32(const float* __restrict__ P, float* hb, float f1, float f2) {
+// ---------------------------------------------------------------------------
+// FP32 on MFMA (v_mfma_f32_16x16x4_f32)
+// ---------------------------------------------------------------------------
+// The layout of the reduced-precision engine (lane l owns sample l % 16 and
+// neurons 16t + 4g + r of a 16-sample tile, g = l / 16), with the K index of
+// each layer's contraction permuted so that every lane's B operand is one of
+// its own outputs of the previous layer: k-step (t, r) pairs lane group g
+// with input neuron 16t + 4g + r, so the A operand of lane l at (output tile
+// T, k-step (t, r)) is W[16T + l % 16][16t + 4 (l / 16) + r].  The four
+// k-steps of a t are four consecutive weights of a row: one 16-byte fragment
+// entry, one global load and one LDS read.  The first and last layers run on
+// the vector ALUs.  What bounds it: the FP32 matrix rate (768 products of 32
+// cycles per 64 samples) and SiLU on the vector ALUs (256 per sample), which
+// overlap little: 2^22 samples 1552 us with single-float fragment reads and
+// the IEEE quotient, 1216 us with this.  In the collide kernel it replaced one
+// sample per lane on the vector ALUs (65 KB of LDS for the activations):
+// 107 us -> 33.9 us on the beam-gas plasma of 2^20 pairs (16 k collisions).
+constexpr int kF32Frag = 3 * 4 * 4 * 64;  // 16-byte entries [layer][T][t][lane], 48 KB
+
+// Parameter index of the first of entry i's four weights.
+__device__ __forceinline__ int f32_frag_src(int i) {
+    const int l = i & 63, t = (i >> 6) & 3, T = (i >> 8) & 3, L = i >> 10;
+    return kOffW2 + L * (kOffW3 - kOffW2) + (16 * T + (l & 15)) * kMlpHidden + 16 * t + 4 * (l >> 4);
+}
+static_assert(kOffW3 - kOffW2 == kOffW4 - kOffW3 && kOffW2 % 4 == 0 && (kOffW3 - kOffW2) % 4 == 0,
+              "hidden matrices evenly spaced, rows 16-byte aligned");
+
+// NTL tiles side by side; amax (nullable): this lane's running max |h| of the
+// inputs of hidden layers 2..4, over the tiles k whose sample is real[k].
+// EXACT: the correctly rounded SiLU (calibration: the FP8 scales come from
+// these values).
+template <int NTL, bool EXACT>
+__device__ __forceinline__ void mlp_tiles_f32(const float4* frag, const float* Ps, const float (&f1)[NTL],
+                                              const float (&f2)[NTL], float (&y0)[NTL], float (&y1)[NTL],
+                                              float* amax, const bool (&real)[NTL]) {
     const int lane = lane_id();
-#pragma unroll 4
-    for (int j = 0; j < kMlpHidden; ++j) {
-        const float z = fmaf(P[kOffW1 + 2 * j + 1], f2, fmaf(P[kOffW1 + 2 * j], f1, P[kOffB1 + j]));
-        hb[j * 64 + lane] = silu_f32(z);
+    const int g = lane >> 4;
+    auto silu = [](float z) { return EXACT ? silu_f32(z) : silu_f32_fast(z); };
+    float h[NTL][16];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const int nb = 16 * t + 4 * g;
+        const float4 wa = ld4(Ps, cW1 + 2 * nb), wb = ld4(Ps, cW1 + 2 * nb + 4), b1 = ld4(Ps, cB1 + nb);
+        const float w1a[4] = {wa.x, wa.z, wb.x, wb.z}, w1b[4] = {wa.y, wa.w, wb.y, wb.w};
+        const float b1v[4] = {b1.x, b1.y, b1.z, b1.w};
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int k = 0; k < NTL; ++k) {
+                h[k][4 * t + r] = silu(fmaf(w1b[r], f2[k], fmaf(w1a[r], f1[k], b1v[r])));
+                if (amax && real[k]) amax[0] = fmaxf(amax[0], fabsf(h[k][4 * t + r]));
+            }
     }
-    const int offW[3] = {kOffW2, kOffW3, kOffW4};
-    const int offB[3] = {kOffB2, kOffB3, kOffB4};
-    float h[kMlpHidden];
-#pragma unroll 1
+    const int offB[3] = {cB2, cB3, cB4};
+#pragma unroll
     for (int L = 0; L < 3; ++L) {
+        float o[NTL][16];
 #pragma unroll
-        for (int k = 0; k < kMlpHidden; ++k) h[k] = hb[k * 64 + lane];
-        const float* W = P + offW[L];
-        const float* B = P + offB[L];
-#pragma unroll 1
-        for (int j = 0; j < kMlpHidden; ++j) {
-            float z = B[j];
+        for (int T = 0; T < 4; ++T) {
+            const float4 b4 = ld4(Ps, offB[L] + 16 * T + 4 * g);
+            floatx4 acc[NTL];
 #pragma unroll
-            for (int k = 0; k < kMlpHidden; ++k) z = fmaf(W[j * kMlpHidden + k], h[k], z);
-            hb[j * 64 + lane] = silu_f32(z);
+            for (int k = 0; k < NTL; ++k) acc[k] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float4 A = frag[((L * 4 + T) * 4 + t) * 64 + lane];
+                const float av[4] = {A.x, A.y, A.z, A.w};
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int k = 0; k < NTL; ++k)
+                        acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[r], h[k][4 * t + r], acc[k], 0, 0, 0);
+            }
+#pragma unroll
+            for (int k = 0; k < NTL; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[k][4 * T + r] = silu(acc[k][r]);
         }
+#pragma unroll
+        for (int k = 0; k < NTL; ++k)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                h[k][j] = o[k][j];
+                if (amax && L < 2 && real[k]) amax[L + 1] = fmaxf(amax[L + 1], fabsf(o[k][j]));
+            }
+    }
+    float p0[NTL], p1[NTL];
+#pragma unroll
+    for (int k = 0; k < NTL; ++k) p0[k] = p1[k] = 0.0f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const float4 v0 = ld4(Ps, cW5 + 16 * t + 4 * g), v1 = ld4(Ps, cW5 + kMlpHidden + 16 * t + 4 * g);
+        const float w50[4] = {v0.x, v0.y, v0.z, v0.w}, w51[4] = {v1.x, v1.y, v1.z, v1.w};
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int k = 0; k < NTL; ++k) {
+                p0[k] = fmaf(w50[r], h[k][4 * t + r], p0[k]);
+                p1[k] = fmaf(w51[r], h[k][4 * t + r], p1[k]);
+            }
     }
 #pragma unroll
-    for (int k = 0; k < kMlpHidden; ++k) h[k] = hb[k * 64 + lane];
-    float a0 = P[kOffB5], a1 = P[kOffB5 + 1];
-#pragma unroll
-    for (int k = 0; k < kMlpHidden; ++k) {
-        a0 = fmaf(P[kOffW5 + k], h[k], a0);
-        a1 = fmaf(P[kOffW5 + kMlpHidden + k], h[k], a1);
+    for (int k = 0; k < NTL; ++k) {
+        float q0 = p0[k], q1 = p1[k];
+        q0 += __shfl_xor(q0, 16, 64);
+        q1 += __shfl_xor(q1, 16, 64);
+        q0 += __shfl_xor(q0, 32, 64);
+        q1 += __shfl_xor(q1, 32, 64);
+        y0[k] = q0 + Ps[cB5];
+        y1[k] = q1 + Ps[cB5 + 1];
     }
-    return make_float2(a0, a1);
 }
 
 // The sampler's reading of the two outputs (cos theta, eps'/eps) at FP32 x,
@@ -336,7 +427,8 @@ struct NetLds {
 };
 template <>
 struct NetLds<CS_SAMPLER_MLP_F32> {
-    float h[4][kMlpHidden * 64];  // one [64][64] buffer per wave (4 waves)
+    float4 frag[kF32Frag];
+    alignas(16) float P[kSmall];  // unscaled
 };
 template <>
 struct NetLds<CS_SAMPLER_MLP_BF16> {
@@ -351,10 +443,15 @@ struct NetLds<CS_SAMPLER_MLP_FP8> {
     float sc[6];
 };
 
-// Fill the network LDS (MFMA precisions); every thread of the block calls it,
-// followed by a barrier.
+// Fill the network LDS; every thread of the block calls it, followed by a
+// barrier.
 template <int SAMP>
 __device__ __forceinline__ void net_load(NetLds<SAMP>& s, const MlpDev& m) {
+    if constexpr (SAMP == CS_SAMPLER_MLP_F32) {
+        for (int i = threadIdx.x; i < kF32Frag; i += blockDim.x)
+            s.frag[i] = *(const float4*)(m.params + f32_frag_src(i));
+        for (int i = threadIdx.x; i < kSmall; i += blockDim.x) s.P[i] = m.params[small_param_src(i)];
+    }
     if constexpr (SAMP == CS_SAMPLER_MLP_BF16 || SAMP == CS_SAMPLER_MLP_FP8) {
         typedef typename FragT<SAMP>::type FT;
         const FT* src = (const FT*)(SAMP == CS_SAMPLER_MLP_BF16 ? m.frag_bf16 : m.frag_fp8);
@@ -368,14 +465,41 @@ __device__ __forceinline__ void net_load(NetLds<SAMP>& s, const MlpDev& m) {
 // kernel can issue its global reads together with its own and wait once:
 // fetch reads this thread's share into registers (every read unconditional,
 // clamped into the arrays), store writes it to LDS; a barrier must follow
-// before the copy is read.  Nothing to do for the other samplers.
-template <int SAMP, int NT, bool MFMA = SAMP == CS_SAMPLER_MLP_BF16 || SAMP == CS_SAMPLER_MLP_FP8>
-struct NetFetch {
+// before the copy is read.  Nothing to do for the plain sampler.
+template <int SAMP, int NT>
+struct NetFetch;
+template <int NT>
+struct NetFetch<CS_SAMPLER_PLAIN, NT> {
     __device__ __forceinline__ void fetch(const MlpDev&) {}
-    __device__ __forceinline__ void store(NetLds<SAMP>&) const {}
+    __device__ __forceinline__ void store(NetLds<CS_SAMPLER_PLAIN>&) const {}
+};
+template <int NT>
+struct NetFetch<CS_SAMPLER_MLP_F32, NT> {
+    static constexpr int kF = kF32Frag / NT, kP = (kSmall + NT - 1) / NT;
+    static_assert(kF * NT == kF32Frag, "whole rounds");
+    float4 f[kF];
+    float p[kP];
+    __device__ __forceinline__ void fetch(const MlpDev& m) {
+#pragma unroll
+        for (int q = 0; q < kF; ++q) f[q] = *(const float4*)(m.params + f32_frag_src((int)threadIdx.x + q * NT));
+#pragma unroll
+        for (int q = 0; q < kP; ++q) {
+            const int i = (int)threadIdx.x + q * NT;
+            p[q] = m.params[small_param_src(i < kSmall ? i : kSmall - 1)];
+        }
+    }
+    __device__ __forceinline__ void store(NetLds<CS_SAMPLER_MLP_F32>& s) const {
+#pragma unroll
+        for (int q = 0; q < kF; ++q) s.frag[threadIdx.x + q * NT] = f[q];
+#pragma unroll
+        for (int q = 0; q < kP; ++q) {
+            const int i = (int)threadIdx.x + q * NT;
+            if (i < kSmall) s.P[i] = p[q];
+        }
+    }
 };
 template <int SAMP, int NT>
-struct NetFetch<SAMP, NT, true> {
+struct NetFetch {
     typedef typename FragT<SAMP>::type FT;
     static constexpr int kF = (kFragCount + NT - 1) / NT;
     static constexpr int kP = (kSmall + NT - 1) / NT;
@@ -411,32 +535,47 @@ struct NetFetch<SAMP, NT, true> {
     }
 };
 
+// NTL tiles of the wave (samples 16 (tile + k) + lane % 16) from the LDS copy.
+template <int SAMP, int NTL>
+__device__ __forceinline__ void net_tiles(NetLds<SAMP>& s, int tile, float f1, float f2, float2& out) {
+    const int lane = lane_id();
+    float g1[NTL], g2[NTL], y0[NTL], y1[NTL];
+#pragma unroll
+    for (int k = 0; k < NTL; ++k) {
+        const int src = 16 * (tile + k) + (lane & 15);
+        g1[k] = __shfl(f1, src, 64);
+        g2[k] = __shfl(f2, src, 64);
+    }
+    if constexpr (SAMP == CS_SAMPLER_MLP_F32) {
+        bool real[NTL] = {};
+        mlp_tiles_f32<NTL, false>(s.frag, s.P, g1, g2, y0, y1, nullptr, real);
+    } else {
+        mlp_tiles<SAMP, NTL>(s.frag, s.P, s.sc, g1, g2, y0, y1);
+    }
+#pragma unroll
+    for (int k = 0; k < NTL; ++k)
+        if ((lane >> 4) == tile + k) out = make_float2(y0[k], y1[k]);
+}
+
 // The network's two outputs for every lane of the wave with need == true
 // (features f1, f2 of the lane's own sample); other lanes get 0.  Must be
-// called by the whole wave (converged).
+// called by the whole wave (converged).  The wave's four tiles are taken two
+// at a time, side by side; a pair of tiles none of whose samples is needed is
+// skipped, and of a pair whose second tile is not needed only the first is
+// evaluated (each tile's arithmetic is that of a lone tile).
 template <int SAMP>
 __device__ __forceinline__ float2 net_outputs(NetLds<SAMP>& s, const MlpDev& m, bool need, float f1, float f2) {
     float2 out = make_float2(0.0f, 0.0f);
-    if constexpr (SAMP == CS_SAMPLER_MLP_F32) {
-        if (__any(need)) out = mlp_lane_f32(m.params, s.h[wave_uniform((int)threadIdx.x >> 6)], f1, f2);
-    } else if constexpr (SAMP == CS_SAMPLER_MLP_BF16 || SAMP == CS_SAMPLER_MLP_FP8) {
-        // the wave's four tiles two at a time, side by side; a pair of tiles
-        // none of whose samples is needed is skipped
-        const int lane = lane_id();
+    if constexpr (SAMP != CS_SAMPLER_PLAIN) {
+        const uint64_t needed = __ballot(need);
 #pragma unroll 1
         for (int tile = 0; tile < 4; tile += 2) {
-            if (!__any(need && (lane >> 5) == (tile >> 1))) continue;
-            float g1[2], g2[2], y0[2], y1[2];
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int src = 16 * (tile + k) + (lane & 15);
-                g1[k] = __shfl(f1, src, 64);
-                g2[k] = __shfl(f2, src, 64);
-            }
-            mlp_tiles<SAMP, 2>(s.frag, s.P, s.sc, g1, g2, y0, y1);
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-                if ((lane >> 4) == tile + k) out = make_float2(y0[k], y1[k]);
+            const uint32_t pair = (uint32_t)(needed >> (16 * tile));
+            if (pair == 0) continue;
+            if ((pair >> 16) == 0)
+                net_tiles<SAMP, 1>(s, tile, f1, f2, out);
+            else
+                net_tiles<SAMP, 2>(s, tile, f1, f2, out);
         }
     }
     return need ? out : make_float2(0.0f, 0.0f);
