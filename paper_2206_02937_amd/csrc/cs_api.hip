@@ -297,8 +297,8 @@ Plan plan_step(int64_t strategy, int64_t chunks_per_block, int64_t pairs_per_lan
     } else if (strategy == CS_STRATEGY_COMPACT) {
         // pair workgroups take G consecutive chunks, a multiple of the pairs
         // per lane and at most kCompactMaxChunks (chunk_cell held one entry
-        // per lane); automatic: the fewest with which every pair workgroup
-        // is resident at once (one round, the waves paced)
+        // per lane); automatic: compact_fit_chunks (every pair workgroup
+        // resident at once: one round, the waves paced)
         const int64_t ppl = sh.pairs_per_lane;
         int64_t Gc = chunks_per_block > 0 ? chunks_per_block : cs::compact_fit_chunks(dtype, ppl, sh.n_chunks);
         Gc = (Gc + ppl - 1) / ppl * ppl;
@@ -646,8 +646,7 @@ cs_status cs_autotune(cs_ctx* ctx, cs_dtype dtype, cs_species electrons, cs_spec
         cand_g[n_cand++] = gpb;
     }
     // compact: (pairs per lane, chunks per pair workgroup), plus for one and
-    // two pairs per lane the fewest chunks with which the pair grid is
-    // resident at once
+    // two pairs per lane the library's own choice
     const int64_t n_chunks_tune = ((electrons.n < photons.n ? electrons.n : photons.n) + 255) / 256;
     for (const auto& pg : {std::pair<int, int>{1, 4}, {1, 8}, {1, 16}, {2, 8}, {2, 16}}) {
         cand_s[n_cand] = CS_STRATEGY_COMPACT;

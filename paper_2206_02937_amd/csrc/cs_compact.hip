@@ -38,7 +38,7 @@ struct CompactArgs {
     int32_t balance;           // pair kernel: pace the waves (the grid is one round of resident workgroups)
     const int32_t* pair_off;
     const uint32_t* keys;
-    const int32_t* chunk_cell;
+    const int32_t* wave_cell;  // first cell of every kWavePairs pairs
     double dt, density_norm;
     uint64_t seed;
     StepControl* ctrl;
@@ -57,113 +57,25 @@ struct CompactArgs {
     MlpDev mlp;
 };
 
-// s_waitcnt immediate that waits for vmcnt 0 only (gfx9 encoding: vmcnt in
-// bits 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 at their maxima).
-constexpr int kWaitVmcnt0 = 0x0F70;
-
-// Read-only data at a wave-uniform index through the constant address space,
-// so that the read is one scalar load (the data do not change while the
-// kernel runs).
-template <typename X>
-__device__ __forceinline__ X ld_uniform(const X* p, int64_t i) {
-    return ((const __attribute__((address_space(4))) X*)p)[i];
-}
-
 // Phases 1 and 2 of one step of the pair kernel for one lane: the pairs of
 // chunks j0 .. j0 + PPL - 1 (one pair of each), their cells, particle ranges
 // and pairing keys, the pairing, and the particle reads -- issued, to be
-// consumed a step later.  The chunk's first cell is the same for the whole
-// wave: its metadata come by scalar loads.  If some lane's pair lies in a
-// later cell, the wave reads the metadata of the chunk's cells (up to 64, one
-// per lane) in one coalesced round trip and each lane finds its own cell
-// among them by a binary search over lane shuffles (chunks of more than 64
-// cells: a binary search per lane in global memory).  `cc`
-// holds chunk_cell[blk G + lane]; c0 is the step's first chunk relative to
-// blk G.  valid == false (uniform) yields inactive slots.
+// consumed a step later.  Lane i of `cc` holds the first cell of the wave's
+// pairs in chunk blk G + i, lane 32 + i that of the 64 pairs after them; c0
+// is the step's first chunk relative to blk G.  valid == false (uniform)
+// yields inactive slots.
 template <typename T, int PPL, bool O32>
-__device__ __forceinline__ void pair_fetch(const CompactArgs<T>& a, bool valid, int64_t j0, int c0, int cc,
+__device__ __forceinline__ void pair_fetch(const CompactArgs<T>& a, bool valid, int32_t j0, int c0, int cc,
                                            int32_t T_total, int tid, PairSlot (&sl)[PPL],
                                            PairRaw<T> (&raw)[PPL]) {
 #pragma unroll
     for (int q = 0; q < PPL; ++q) {
-        const int64_t j = j0 + q;
-        const int32_t t = (int32_t)(j * kChunk) + tid;
-        const bool jv = valid && j < a.n_chunks && j * kChunk < (int64_t)T_total;  // uniform
-        const bool act = jv && t < T_total;
-        int64_t e0 = 0, e1 = 0, g0 = 0, g1 = 0;
-        uint4 key = make_uint4(0, 0, 0, 0);
-        int32_t po = 0, po_next = 0;
-        if (jv) {
-            const int cs0 = __builtin_amdgcn_readlane(cc, c0 + q);
-            e0 = ld_uniform(a.off_e, cs0);
-            e1 = ld_uniform(a.off_e, cs0 + 1);
-            g0 = ld_uniform(a.off_g, cs0);
-            g1 = ld_uniform(a.off_g, cs0 + 1);
-            key = make_uint4(ld_uniform(a.keys, 4 * cs0), ld_uniform(a.keys, 4 * cs0 + 1),
-                             ld_uniform(a.keys, 4 * cs0 + 2), ld_uniform(a.keys, 4 * cs0 + 3));
-            po = ld_uniform(a.pair_off, cs0);
-            po_next = ld_uniform(a.pair_off, cs0 + 1);
-            const int ch = __builtin_amdgcn_readlane(cc, c0 + q + 1);
-            const int nc = ch - cs0 + 1;  // cells cs0 .. ch hold the chunk's pairs
-            if (__any(act && t >= po_next)) {
-                if (nc <= 64) {
-                    // lane l reads cell cs0 + l's metadata (one coalesced
-                    // round trip); each lane finds its cell among them by
-                    // a binary search over the wave's pair offsets and takes
-                    // that cell's values by lane shuffles
-                    const int cl = cs0 + (lane_id() < nc ? lane_id() : nc - 1);
-                    const int32_t po_l = a.pair_off[cl];
-                    const int64_t e0_l = a.off_e[cl], g0_l = a.off_g[cl];
-                    const int32_t ne_l = (int32_t)(a.off_e[cl + 1] - e0_l), ng_l = (int32_t)(a.off_g[cl + 1] - g0_l);
-                    const uint4 key_l = *(const uint4*)(a.keys + 4 * cl);
-                    int lo = 0, hi = nc - 1;
-#pragma unroll
-                    for (int it = 0; it < 6; ++it) {  // nc <= 64 = 2^6
-                        const int mid = (lo + hi + 1) >> 1;
-                        if (__shfl(po_l, mid, 64) <= t)
-                            lo = mid;
-                        else
-                            hi = mid - 1;
-                    }
-                    // (shuffles by the whole wave, then the selection)
-                    const int64_t e0c = (int64_t)__shfl((unsigned long long)e0_l, lo, 64);
-                    const int64_t g0c = (int64_t)__shfl((unsigned long long)g0_l, lo, 64);
-                    const int32_t nec = __shfl(ne_l, lo, 64), ngc = __shfl(ng_l, lo, 64);
-                    const uint4 keyc = make_uint4(__shfl(key_l.x, lo, 64), __shfl(key_l.y, lo, 64),
-                                                  __shfl(key_l.z, lo, 64), __shfl(key_l.w, lo, 64));
-                    const int32_t poc = __shfl(po_l, lo, 64);
-                    if (act && t >= po_next) {
-                        e0 = e0c;
-                        g0 = g0c;
-                        e1 = e0c + nec;
-                        g1 = g0c + ngc;
-                        key = keyc;
-                        po = poc;
-                    }
-                } else if (act && t >= po_next) {
-                    // more than 64 cells in the chunk: per-lane binary search
-                    int lo = cs0 + 1, hi = ch;
-                    while (lo < hi) {
-                        const int mid = (lo + hi + 1) >> 1;
-                        if (a.pair_off[mid] <= t)
-                            lo = mid;
-                        else
-                            hi = mid - 1;
-                    }
-                    e0 = a.off_e[lo];
-                    e1 = a.off_e[lo + 1];
-                    g0 = a.off_g[lo];
-                    g1 = a.off_g[lo + 1];
-                    key = *(const uint4*)(a.keys + 4 * lo);
-                    po = a.pair_off[lo];
-                }
-                // complete these reads inside the branch, so that no read of
-                // it is still counted as possibly in flight after it (which
-                // would make later waits include the particle reads)
-                __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-            }
-        }
-        sl[q] = pair_index(act, e0, e1, g0, g1, key.x, key.y, key.z, key.w, (uint32_t)(t - po));
+        // (chunks and pairs number below 2^31)
+        const int32_t t_wave = (j0 + q) * kChunk + (wave_uniform(tid >> 6) << 6);  // the wave's first pair
+        sl[q] = PairSlot{0, 0, 0, false};
+        if (valid && t_wave < T_total)  // uniform
+            sl[q] = pair_slots(a, t_wave, T_total, __builtin_amdgcn_readlane(cc, c0 + q),
+                               __builtin_amdgcn_readlane(cc, 32 + c0 + q));
         raw[q] = pair_load_all<T, O32>(a.pt, sl[q]);
     }
 }
@@ -196,6 +108,14 @@ __device__ __forceinline__ void balance_priority(int rem) {
 // (64 G slots) in the order it meets them; after the last step one look-back
 // places the workgroup's slots (wave 0's, then wave 1's, ...) in the dense
 // list, whose entry q names the stash slot of accepted pair q.
+//
+// Bound by the vector instructions (about 80 % of a compute unit's busy
+// time), 244 per 64 pairs with 256-pair cells and 390 with ragged 64-pair
+// ones; the pairing and the reads are 25 of its 41 us at 2^22 pairs.  At 80
+// vector registers six waves fit a SIMD (five at 91, with log1p's constants
+// in s(x)).  FP32 storage, plain sampler: 2^22 pairs in 256-pair cells 46.1 ->
+// 41.2 us, in 64-pair cells of uneven filling 85.5 -> 68.7 us, 2^24 pairs
+// 208.7 -> 194.6 us.
 template <typename T, int PPL, bool O32>
 __global__ __launch_bounds__(kChunk) void k_pair_compact(const CompactArgs<T> a) {
     __shared__ double s_sig[kSigTabSegments * kSigTabTerms];
@@ -216,10 +136,10 @@ __global__ __launch_bounds__(kChunk) void k_pair_compact(const CompactArgs<T> a)
     double sig_v[kSigRounds];
 #pragma unroll
     for (int r = 0; r < kSigRounds; ++r) sig_v[r] = kSigTab[tid + r * kChunk];
-    // chunk_cell of the workgroup's chunks and of the one after them, lane i
-    // holding entry blk G + i (G < 64)
-    const int64_t jc = blk * G + lane;
-    const int cc = lane <= G && jc <= a.n_chunks ? a.chunk_cell[jc] : 0;
+    // the first cells of the wave's 64 pairs of each chunk and of the 64 pairs
+    // after them (G <= 32: see pair_fetch)
+    const int64_t jc = (blk * G + (lane & 31)) * (kChunk / kWavePairs) + wave + (lane >> 5);
+    const int cc = (lane & 31) < G && jc <= a.n_chunks * (kChunk / kWavePairs) ? a.wave_cell[jc] : 0;
     const int32_t T_read = a.pair_off[a.n_cells];  // read with the control block, not after it
     StepControl* ctrl = a.ctrl;
     const CtrlView cv = ctrl_view(ctrl);
@@ -241,16 +161,16 @@ __global__ __launch_bounds__(kChunk) void k_pair_compact(const CompactArgs<T> a)
     int n_stage = 0;  // wave-uniform
     const uint64_t lanes_below = (1ull << lane) - 1ull;
     double sum_p = 0.0;
-    long long n_clip = 0, n_inv = 0;
+    int n_clip = 0, n_inv = 0;  // wave-uniform (at most 64 G)
     // physics of one step; accepted pairs go to the wave's stash region
     auto physics = [&](const PairSlot(&sl)[PPL], const PairRaw<T>(&raw)[PPL]) {
 #pragma unroll
         for (int q = 0; q < PPL; ++q) {
             const PairOutcome o = pair_physics<T>(sl[q], raw[q], a.dt, a.density_norm, a.seed, step, s_sig);
             sum_p += o.P;
-            n_clip += o.clipped ? 1 : 0;
-            n_inv += o.invalid ? 1 : 0;
-            const uint64_t mask = __ballot(o.accept);
+            n_clip += __popcll(__builtin_amdgcn_ballot_w64(o.clipped));
+            n_inv += __popcll(__builtin_amdgcn_ballot_w64(o.invalid));
+            const uint64_t mask = __builtin_amdgcn_ballot_w64(o.accept);
             if (o.accept) stage[n_stage + __popcll(mask & lanes_below)] = make_stash<T>(sl[q], raw[q]);
             n_stage += __popcll(mask);
         }
@@ -258,26 +178,26 @@ __global__ __launch_bounds__(kChunk) void k_pair_compact(const CompactArgs<T> a)
     // two register sets in turn (no copies, which would wait for the reads)
     PairSlot sl_a[PPL], sl_b[PPL];
     PairRaw<T> raw_a[PPL], raw_b[PPL];
-    pair_fetch<T, PPL, O32>(a, n_steps > 0, blk * G, 0, cc, T_total, tid, sl_a, raw_a);
+    const int32_t j_blk = (int32_t)(blk * G);  // (chunks number below 2^23)
+    pair_fetch<T, PPL, O32>(a, n_steps > 0, j_blk, 0, cc, T_total, tid, sl_a, raw_a);
     __syncthreads();  // s_sig
     for (int st = 0; st < n_steps; st += 2) {
-        pair_fetch<T, PPL, O32>(a, st + 1 < n_steps, blk * G + (st + 1) * PPL, (st + 1) * PPL, cc, T_total, tid, sl_b,
-                           raw_b);
+        pair_fetch<T, PPL, O32>(a, st + 1 < n_steps, j_blk + (st + 1) * PPL, (st + 1) * PPL, cc, T_total, tid, sl_b,
+                                raw_b);
         if (a.balance) balance_priority(n_steps - st);
         physics(sl_a, raw_a);
         if (st + 1 >= n_steps) break;
-        pair_fetch<T, PPL, O32>(a, st + 2 < n_steps, blk * G + (st + 2) * PPL, (st + 2) * PPL, cc, T_total, tid, sl_a,
-                           raw_a);
+        pair_fetch<T, PPL, O32>(a, st + 2 < n_steps, j_blk + (st + 2) * PPL, (st + 2) * PPL, cc, T_total, tid, sl_a,
+                                raw_a);
         if (a.balance) balance_priority(n_steps - st - 1);
         physics(sl_b, raw_b);
     }
     __builtin_amdgcn_s_setprio(0);
     const double wp = wave_sum(sum_p);
-    const long long wc = wave_sum_i(n_clip), wi = wave_sum_i(n_inv);
     if (lane == 0) {
         s_rd[wave] = wp;
-        s_ri[2 * wave] = wc;
-        s_ri[2 * wave + 1] = wi;
+        s_ri[2 * wave] = n_clip;
+        s_ri[2 * wave + 1] = n_inv;
         s_wcnt[wave] = n_stage;
     }
     __syncthreads();
@@ -550,7 +470,7 @@ size_t compact_workspace_bytes(const StepShape& s) {
     size_t b = 0;
     b += al(sizeof(int32_t) * (s.n_cells + 1));
     b += al(sizeof(uint32_t) * 4 * (s.n_cells > 0 ? s.n_cells : 1));
-    b += al(sizeof(int32_t) * (s.n_chunks + 1));
+    b += al(sizeof(int32_t) * (s.n_chunks * (kChunk / kWavePairs) + 1));
     b += al(sizeof(int32_t) * compact_list_len(s) + 8);
     b += al(sizeof(int32_t) * seg_count_len(s));
     b += al(compact_stash_bytes(s) + 16);
@@ -570,7 +490,7 @@ void carve_compact_buffers(const Workspace& w, const StepShape& s, CompactBuffer
     };
     b->pair_off = (int32_t*)take(sizeof(int32_t) * (s.n_cells + 1));
     b->cell_keys = (uint32_t*)take(sizeof(uint32_t) * 4 * (s.n_cells > 0 ? s.n_cells : 1));
-    b->chunk_cell = (int32_t*)take(sizeof(int32_t) * (s.n_chunks + 1));
+    b->wave_cell = (int32_t*)take(sizeof(int32_t) * (s.n_chunks * (kChunk / kWavePairs) + 1));
     b->list = (int32_t*)take(sizeof(int32_t) * compact_list_len(s) + 8);
     b->seg_count = (int32_t*)take(sizeof(int32_t) * seg_count_len(s));
     b->stash = take(compact_stash_bytes(s) + 16);
@@ -582,37 +502,63 @@ void carve_compact_buffers(const Workspace& w, const StepShape& s, CompactBuffer
     b->coll_fb = (int64_t*)take(8 * s.n_collide_blocks);
 }
 
-// Workgroups of k_pair_compact<T, PPL, O32> resident at once on the current
-// device (its compute units times the kernel's occupancy), computed once.
+// Workgroups of k_pair_compact<T, PPL, O32> resident at once on a compute unit
+// of the current device, and its compute units; computed once.
+struct Resident {
+    int64_t per_cu, cus;
+};
+
 template <typename T, int PPL, bool O32 = true>
-static int64_t pair_resident_blocks() {
-    static int64_t cached = -1;
-    if (cached < 0) {
+static Resident pair_resident() {
+    static int64_t per_cu_cached = -1, cus_cached = -1;
+    if (per_cu_cached < 0 || cus_cached < 0) {
         int dev = 0, n_cu = 0, per_cu = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(
                 &per_cu, reinterpret_cast<const void*>(&k_pair_compact<T, PPL, O32>), kChunk, 0) != hipSuccess)
-            return 0;  // unknown: no pacing
-        cached = (int64_t)n_cu * per_cu;
+            return {0, 0};  // unknown: no pacing
+        per_cu_cached = per_cu;
+        cus_cached = n_cu;
     }
-    return cached;
+    return {per_cu_cached, cus_cached};
 }
 
+template <typename T, int PPL, bool O32 = true>
+static int64_t pair_resident_blocks() {
+    const Resident r = pair_resident<T, PPL, O32>();
+    return r.per_cu * r.cus;
+}
+
+// From the fewest chunks with which every workgroup is resident, to the value
+// that gives the busiest compute unit the fewest chunks, as long as it keeps
+// four workgroups (FP32 storage, six resident per compute unit: 4096 chunks take
+// 21.0 us at 3 each, 6 workgroups and 18 chunks on the busiest unit, and 18.3
+// at 4 each, 4 and 16; 16384 chunks 41.3 at 11 each (66), 43.7 at 12 (72), 40.4
+// at 16 (64), 44.3 at 22 (66 again, by 3 workgroups)).
 int64_t compact_fit_chunks(cs_dtype dtype, int64_t ppl, int64_t n_chunks) {
-    int64_t r;
+    Resident r;
     if (dtype == CS_F64)
-        r = ppl == 1 ? pair_resident_blocks<double, 1>()
-                     : ppl == 2 ? pair_resident_blocks<double, 2>() : pair_resident_blocks<double, 4>();
+        r = ppl == 1 ? pair_resident<double, 1>() : ppl == 2 ? pair_resident<double, 2>() : pair_resident<double, 4>();
     else
-        r = ppl == 1 ? pair_resident_blocks<float, 1>()
-                     : ppl == 2 ? pair_resident_blocks<float, 2>() : pair_resident_blocks<float, 4>();
-    if (r <= 0) r = 1024;
-    int64_t g = (n_chunks + r - 1) / r;
+        r = ppl == 1 ? pair_resident<float, 1>() : ppl == 2 ? pair_resident<float, 2>() : pair_resident<float, 4>();
+    if (r.per_cu <= 0 || r.cus <= 0) r = {4, 256};
+    const int64_t resident = r.per_cu * r.cus;
+    int64_t g = (n_chunks + resident - 1) / resident;
     g = (g + ppl - 1) / ppl * ppl;
     if (g < ppl) g = ppl;
-    if (g > kCompactMaxChunks) g = kCompactMaxChunks / ppl * ppl;
-    return g;
+    if (g > kCompactMaxChunks) return kCompactMaxChunks / ppl * ppl;
+    int64_t best = -1, busiest = 0;
+    for (; g <= kCompactMaxChunks; g += ppl) {
+        const int64_t blocks = (n_chunks + g - 1) / g, on_cu = (blocks + r.cus - 1) / r.cus;
+        if (best > 0 && (on_cu < 4 || on_cu * g >= busiest)) {
+            if (on_cu < 4) break;
+            continue;
+        }
+        best = g;
+        busiest = on_cu * g;
+    }
+    return best;
 }
 
 // 32-bit byte offsets into the particle arrays whenever both species fit
@@ -639,7 +585,7 @@ static hipError_t launch_compact_t(const StepShape& sh, const CompactBuffers& b,
     };
     mark(0);
     // prep status words first, then the pair workgroups' (kPairStatusStride apart)
-    hipError_t e = launch_prep(sh, b.ctrl, b.status, b.pair_off, b.cell_keys, b.chunk_cell, p, st);
+    hipError_t e = launch_prep(sh, b.ctrl, b.status, b.pair_off, b.cell_keys, b.wave_cell, kWavePairs, p, st);
     if (e != hipSuccess) return e;
     mark(1);
     CompactArgs<T> a;
@@ -651,7 +597,7 @@ static hipError_t launch_compact_t(const StepShape& sh, const CompactBuffers& b,
     a.chunks_per_block = (int32_t)sh.chunks_per_block;
     a.pair_off = b.pair_off;
     a.keys = b.cell_keys;
-    a.chunk_cell = b.chunk_cell;
+    a.wave_cell = b.wave_cell;
     a.dt = p.dt;
     a.density_norm = p.density_norm;
     a.seed = p.seed;

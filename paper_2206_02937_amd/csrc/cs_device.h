@@ -18,6 +18,12 @@
 
 namespace cs {
 
+// The lanes in which a comparison holds, and whether it holds in any: scalar
+// tests of the compare's mask.  Masks of several conditions are combined as
+// scalars (a combined condition would pass through a vector register).
+__device__ __forceinline__ uint64_t lanes(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+__device__ __forceinline__ bool any_lane(bool p) { return lanes(p) != 0; }
+
 // ---------------------------------------------------------------------------
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of the 4x32
 // S-box, key advanced by the Weyl constants between rounds.
@@ -73,7 +79,7 @@ __device__ __forceinline__ u32x4 draw(uint64_t seed, uint64_t index, uint64_t st
 
 // 53-bit uniform in [0, 1): top 27 bits of a, top 26 bits of b.
 __device__ __forceinline__ double uniform53(uint32_t a, uint32_t b) {
-    return ((double)(a >> 5) * 67108864.0 + (double)(b >> 6)) * 0x1p-53;
+    return fma((double)(a >> 5), 67108864.0, (double)(b >> 6)) * 0x1p-53;
 }
 
 // ---------------------------------------------------------------------------
@@ -100,23 +106,28 @@ struct FeistelKey {
 
 __device__ __forceinline__ uint32_t ceil_log2(uint32_t M) { return M <= 1 ? 0u : 32u - __clz(M - 1u); }
 
+// One pass of the network: the permutation of [0, 2^b) at v.
+__device__ __forceinline__ uint32_t feistel(uint32_t v, const FeistelKey& key) {
+    const uint32_t a = key.bits >> 1, c = key.bits - a;
+    const uint32_t mask_a = (1u << a) - 1u, mask_c = (1u << c) - 1u;
+    uint32_t L = v >> c, R = v & mask_c;  // widths a, c
+#pragma unroll
+    for (int r = 0; r < 4; r += 2) {
+        const uint32_t R1 = L ^ (fmix32(R ^ key.k[r]) & mask_a);  // (L, R) -> (R, R1): widths c, a
+        const uint32_t R2 = R ^ (fmix32(R1 ^ key.k[r + 1]) & mask_c);  // -> (R1, R2): widths a, c
+        L = R1;
+        R = R2;
+    }
+    return (L << c) | R;
+}
+
 // The cycle-walk always ends: i lies on a cycle of the permutation of
 // [0, 2^b), and that cycle returns to i, which is < M.
 __device__ __forceinline__ uint32_t shuffle_index(uint32_t i, uint32_t M, const FeistelKey& key) {
     if (M <= 1u) return 0u;
-    const uint32_t a = key.bits >> 1, c = key.bits - a;
-    const uint32_t mask_a = (1u << a) - 1u, mask_c = (1u << c) - 1u;
     uint32_t v = i;
     do {
-        uint32_t L = v >> c, R = v & mask_c;  // widths a, c
-#pragma unroll
-        for (int r = 0; r < 4; r += 2) {
-            const uint32_t R1 = L ^ (fmix32(R ^ key.k[r]) & mask_a);  // (L, R) -> (R, R1): widths c, a
-            const uint32_t R2 = R ^ (fmix32(R1 ^ key.k[r + 1]) & mask_c);  // -> (R1, R2): widths a, c
-            L = R1;
-            R = R2;
-        }
-        v = (L << c) | R;
+        v = feistel(v, key);
     } while (v >= M);
     return v;
 }
@@ -163,43 +174,6 @@ __device__ __forceinline__ double recip_approx(double a) {
     return fma(fma(-a, r, 1.0), r, r);
 }
 
-// s(x) = sigma_KN(x) / sigma_T.  Below 2: the per-segment Taylor polynomial
-// of cs_sigma_table.h, evaluated per lane (each lane loads its own segment's
-// 12 coefficients; no lane waits for another's branch).  `tab` is kSigTab or
-// a copy of it (e.g. in LDS): the same coefficients, the same result.  From
-// 2 to 2^17 the second table (segment index and centre from the exponent and
-// the top four mantissa bits); above, the closed form with log1p.
-__device__ __forceinline__ double sigma_ratio_tab(double x, const double* tab) {
-    if (x < kSigTabMax) {
-        int j = (int)(x * kSigTabInvWidth);
-        j = j < 0 ? 0 : (j > kSigTabSegments - 1 ? kSigTabSegments - 1 : j);
-        const double t = x - ((double)j + 0.5) / kSigTabInvWidth;
-        const double* a = tab + j * kSigTabTerms;
-        double acc = a[kSigTabTerms - 1];
-#pragma unroll
-        for (int n = kSigTabTerms - 2; n >= 0; --n) acc = fma(acc, t, a[n]);
-        return acc;
-    }
-    if (x < kSigTabHiMax) {
-        // (hi >> 16) = (1023 + e) << 4 | m for x = 2^e (1 + m/16 + ...)
-        const int hi = __double2hiint(x);
-        const int j = (hi >> 16) - ((1023 + 1) << 4);
-        const double t = x - __hiloint2double((hi & (int)0xFFFF0000) | 0x8000, 0);
-        const double* a = kSigTabHi + j * kSigTabTerms;
-        double acc = a[kSigTabTerms - 1];
-#pragma unroll
-        for (int n = kSigTabTerms - 2; n >= 0; --n) acc = fma(acc, t, a[n]);
-        return acc;
-    }
-    const double l = log1p(2.0 * x);
-    const double opx = 1.0 + x, o2x = 1.0 + 2.0 * x;
-    return 0.75 * (opx / (x * x * x) * (2.0 * x * opx / o2x - l) + l / (2.0 * x) - (1.0 + 3.0 * x) / (o2x * o2x));
-}
-
-__device__ __forceinline__ double sigma_ratio(double x) { return sigma_ratio_tab(x, kSigTab); }
-
-// Whether p holds in an active lane (a scalar test of the compare's mask).
-__device__ __forceinline__ bool any_lane(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
 
 // P(sigma) for 0 <= sigma < 1/4.  sigma <= 1.5e-3: the first six terms of
 // the series (remainder below 1e-17), else the degree-15 polynomial in two
@@ -291,6 +265,41 @@ __device__ __forceinline__ KnTail kn_tail(double v, double x) {
     if (any_lane(big)) return kn_tail_z<true>(v, x, z, big);
     return kn_tail_z<false>(v, x, z, false);
 }
+
+// s(x) = sigma_KN(x) / sigma_T.  Below 2: the per-segment Taylor polynomial
+// of cs_sigma_table.h, evaluated per lane (each lane loads its own segment's
+// 12 coefficients; no lane waits for another's branch).  `tab` is kSigTab or
+// a copy of it (e.g. in LDS): the same coefficients, the same result.  From
+// 2 to 2^17 the second table (segment index and centre from the exponent and
+// the top four mantissa bits); above, the whole angular integral (3/8) T(2),
+// whose coefficients come by scalar loads (log1p's, held in vector registers
+// across the pair kernel's loop, cost it a wave per SIMD).
+__device__ __forceinline__ double sigma_ratio_tab(double x, const double* tab) {
+    if (x < kSigTabMax) {
+        int j = (int)(x * kSigTabInvWidth);
+        j = j < 0 ? 0 : (j > kSigTabSegments - 1 ? kSigTabSegments - 1 : j);
+        const double t = x - ((double)j + 0.5) / kSigTabInvWidth;
+        const double* a = tab + j * kSigTabTerms;
+        double acc = a[kSigTabTerms - 1];
+#pragma unroll
+        for (int n = kSigTabTerms - 2; n >= 0; --n) acc = fma(acc, t, a[n]);
+        return acc;
+    }
+    if (x < kSigTabHiMax) {
+        // (hi >> 16) = (1023 + e) << 4 | m for x = 2^e (1 + m/16 + ...)
+        const int hi = __double2hiint(x);
+        const int j = (hi >> 16) - ((1023 + 1) << 4);
+        const double t = x - __hiloint2double((hi & (int)0xFFFF0000) | 0x8000, 0);
+        const double* a = kSigTabHi + j * kSigTabTerms;
+        double acc = a[kSigTabTerms - 1];
+#pragma unroll
+        for (int n = kSigTabTerms - 2; n >= 0; --n) acc = fma(acc, t, a[n]);
+        return acc;
+    }
+    return 0.375 * kn_tail(2.0, x).T;
+}
+
+__device__ __forceinline__ double sigma_ratio(double x) { return sigma_ratio_tab(x, kSigTab); }
 
 // (8/3) s(x) = T(2): the whole angular integral.
 __device__ __forceinline__ double kn_total(double x) {
@@ -516,12 +525,15 @@ __device__ __forceinline__ XFlux x_flux_impl(d3 p, d3 k, double pp, double kk) {
     return r;
 }
 
-// The fast form wherever (1 + p.p) k.k lies in [1e-300, 1e300] (then every
-// operand above is normal); the IEEE square root and division outside.
+// The range of a = (1 + p.p) k.k in which every operand of the fast form is
+// normal.
+constexpr double kFluxNormalMin = 1e-300, kFluxNormalMax = 1e300;
+
+// The fast form there; the IEEE square root and division outside.
 __device__ __forceinline__ XFlux x_flux(d3 p, d3 k, double pp, double kk) {
     if (kk == 0.0) return {0.0, 0.0};
     const double a = (1.0 + pp) * kk;
-    if (a >= 1e-300 && a <= 1e300) return x_flux_impl<true>(p, k, pp, kk);
+    if (a >= kFluxNormalMin && a <= kFluxNormalMax) return x_flux_impl<true>(p, k, pp, kk);
     return x_flux_impl<false>(p, k, pp, kk);
 }
 

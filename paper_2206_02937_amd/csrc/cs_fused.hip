@@ -4,7 +4,7 @@
 //   k_prep_scan  one pass over the cells: validate offsets, pairs per cell
 //                (min(N_e, N_g)), pairing keys, exclusive scan of the pair
 //                counts by decoupled look-back, and the first cell of every
-//                256-pair chunk.
+//                256-pair chunk (64-pair wave for the compact strategy).
 //   k_step       persistent over chunks: each workgroup evaluates `chunks`
 //                consecutive 256-pair chunks (pairing, x, s(x), P, accept),
 //                appends accepted pairs in pair order to a queue in LDS, and
@@ -34,15 +34,18 @@ namespace cs {
 constexpr int kPrepThreads = 256;
 constexpr int kPrepPerThread = 1;
 constexpr int kPrepCells = kPrepThreads * kPrepPerThread;
+constexpr int kPrepOwn = 8;  // cell-map entries a lane writes by itself
 
 struct PrepArgs {
     const int64_t *off_e, *off_g;
-    int64_t n_cells, ne, ng, n_chunks;
+    int64_t n_cells, ne, ng;
     uint64_t seed, step;
     int use_device_step;  // 1: take the step from ctrl (graph replay)
     int32_t* pair_off;    // [n_cells + 1]
     uint32_t* keys;       // [4 n_cells]
-    int32_t* chunk_cell;  // [n_chunks + 1]
+    int32_t* cell_map;    // [n_units + 1]: first cell of every `unit` pairs
+    int64_t n_units;
+    int unit_log2;
     uint64_t* status;     // [n_prep_blocks]
     StepControl* ctrl;
 };
@@ -98,22 +101,34 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep_scan(const PrepArgs a) {
         const int64_t c = base + r;
         if (c < a.n_cells) {
             a.pair_off[c] = run;
-            // chunks whose first pair lies in this cell start here
-            if (cnt[r] > 0) {
-                const int64_t j0 = ((int64_t)run + kChunk - 1) / kChunk;
-                const int64_t j1 = ((int64_t)run + cnt[r] + kChunk - 1) / kChunk;
-                for (int64_t j = j0; j < j1; ++j) a.chunk_cell[j] = (int32_t)c;
-            }
         }
+        // units whose first pair lies in this cell start here: the lane's own
+        // few one by one, a long run of a large cell by the whole wave
+        const int up = (1 << a.unit_log2) - 1;
+        int64_t j0 = ((int64_t)run + up) >> a.unit_log2;
+        int64_t j1 = ((int64_t)run + cnt[r] + up) >> a.unit_log2;
+        // (an invalid layout's counts can add up to more than the map holds)
+        if (j0 < 0) j0 = 0;
+        if (j1 > a.n_units + 1) j1 = a.n_units + 1;
+        uint64_t longs = __builtin_amdgcn_ballot_w64(j1 - j0 > kPrepOwn);
+        while (longs) {
+            const int l = (int)__ffsll((unsigned long long)longs) - 1;
+            longs &= longs - 1;
+            const int32_t b0 = __builtin_amdgcn_readlane((int)j0, l), b1 = __builtin_amdgcn_readlane((int)j1, l);
+            const int32_t bc = (int32_t)(base - (int64_t)lane_id() * kPrepPerThread + (int64_t)l * kPrepPerThread + r);
+            for (int32_t j = b0 + lane_id(); j < b1; j += 64) a.cell_map[j] = bc;
+        }
+        if (j1 - j0 <= kPrepOwn)
+            for (; j0 < j1; ++j0) a.cell_map[j0] = (int32_t)c;
         run += cnt[r];
     }
     if (blockIdx.x == gridDim.x - 1) {
         // this block's inclusive prefix is the total pair count T
         const int T = s_prefix + block_total;
         if (threadIdx.x == 0) a.pair_off[a.n_cells] = T;
-        const int64_t jt = ((int64_t)T + kChunk - 1) / kChunk;
-        for (int64_t j = jt + threadIdx.x; j <= a.n_chunks; j += kPrepThreads)
-            a.chunk_cell[j] = (int32_t)(a.n_cells - 1);
+        const int64_t jt = ((int64_t)T + (1 << a.unit_log2) - 1) >> a.unit_log2;
+        for (int64_t j = jt + threadIdx.x; j <= a.n_units; j += kPrepThreads)
+            a.cell_map[j] = (int32_t)(a.n_cells - 1);
     }
 }
 
@@ -454,7 +469,7 @@ void carve_fused_buffers(const Workspace& w, const StepShape& s, FusedBuffers* b
 }
 
 hipError_t launch_prep(const StepShape& sh, StepControl* ctrl, uint64_t* status, int32_t* pair_off, uint32_t* keys,
-                       int32_t* chunk_cell, const StepParams& p, hipStream_t st) {
+                       int32_t* cell_map, int unit, const StepParams& p, hipStream_t st) {
     if (sh.n_cells <= 0) return hipSuccess;
     PrepArgs pa;
     pa.off_e = p.off_e;
@@ -462,13 +477,14 @@ hipError_t launch_prep(const StepShape& sh, StepControl* ctrl, uint64_t* status,
     pa.n_cells = sh.n_cells;
     pa.ne = sh.ne;
     pa.ng = sh.ng;
-    pa.n_chunks = sh.n_chunks;
+    pa.n_units = sh.n_chunks * (kChunk / unit);
+    pa.unit_log2 = __builtin_ctz((unsigned)unit);
     pa.seed = p.seed;
     pa.step = p.step;
     pa.use_device_step = p.use_device_step;
     pa.pair_off = pair_off;
     pa.keys = keys;
-    pa.chunk_cell = chunk_cell;
+    pa.cell_map = cell_map;
     pa.status = status;
     pa.ctrl = ctrl;
     k_prep_scan<<<(unsigned)fused_prep_blocks(sh.n_cells), kPrepThreads, 0, st>>>(pa);
@@ -481,7 +497,7 @@ static hipError_t launch_fused_t(const StepShape& sh, const FusedBuffers& b, con
         if (p.events) (void)hipEventRecord(p.events[i], st);
     };
     mark(0);
-    hipError_t e = launch_prep(sh, b.ctrl, b.status, b.pair_off, b.cell_keys, b.chunk_cell, p, st);
+    hipError_t e = launch_prep(sh, b.ctrl, b.status, b.pair_off, b.cell_keys, b.chunk_cell, kChunk, p, st);
     if (e != hipSuccess) return e;
     mark(1);
     FusedArgs<T> fa;
@@ -619,7 +635,7 @@ static hipError_t launch_cell_t(const StepShape& sh, const FusedBuffers& b, cons
         if (p.events) (void)hipEventRecord(p.events[i], st);
     };
     mark(0);
-    hipError_t e = launch_prep(sh, b.ctrl, b.status, b.pair_off, b.cell_keys, b.chunk_cell, p, st);
+    hipError_t e = launch_prep(sh, b.ctrl, b.status, b.pair_off, b.cell_keys, b.chunk_cell, kChunk, p, st);
     if (e != hipSuccess) return e;
     mark(1);
     FusedArgs<T> fa = {};

@@ -13,6 +13,7 @@
 namespace cs {
 
 constexpr int kChunk = 256;       // pairs per workgroup of the pair kernel
+constexpr int kWavePairs = 64;    // pairs per wave of it: granularity of the compact strategy's cell map
 constexpr int64_t kCompactMaxChunks = 32;  // compact pair kernel: chunks per workgroup
 constexpr int kPairStatusStride = 16;      // compact pair kernel: look-back status words apart (one 128-byte line each)
 constexpr int64_t kTimingRing = 512;  // steps whose stage events are kept
@@ -107,7 +108,7 @@ struct CompactBuffers {
     uint64_t* status;     // prep blocks, then one word per chunk
     int32_t* pair_off;    // [n_cells + 1]
     uint32_t* cell_keys;  // [4 n_cells]
-    int32_t* chunk_cell;  // [n_chunks + 1]
+    int32_t* wave_cell;   // [n_chunks * kChunk / kWavePairs + 1] first cell of every kWavePairs pairs
     int32_t* list;        // [n_chunks * kChunk] stash slots of the accepted pairs, dense (workgroup, wave, pair order)
     void* stash;          // accepted pairs with their particle values: 64 G slots per pair-kernel wave
     int32_t* seg_count;   // [pair workgroups + 1] accepted pairs per pair workgroup (segmented list)
@@ -120,9 +121,10 @@ struct CompactBuffers {
 };
 
 int64_t compact_collide_threads(cs_sampler s);
-// compact: the fewest chunks per pair workgroup (a multiple of the pairs per
-// lane, at most kCompactMaxChunks) with which every pair workgroup of
-// n_chunks chunks is resident at once on the current device
+// compact: chunks per pair workgroup (a multiple of the pairs per lane, at
+// most kCompactMaxChunks) when the caller leaves them to the library: few
+// enough for an even load, enough for every pair workgroup of n_chunks chunks
+// to be resident at once on the current device
 int64_t compact_fit_chunks(cs_dtype dtype, int64_t ppl, int64_t n_chunks);
 int64_t compact_pair_blocks(const StepShape& s);
 size_t fused_workspace_bytes(const StepShape& s);
@@ -188,8 +190,10 @@ hipError_t launch_finalize(const FinalArgs& f, hipStream_t st);
 size_t compact_workspace_bytes(const StepShape& s);
 void carve_compact_buffers(const Workspace& w, const StepShape& s, CompactBuffers* b);
 hipError_t launch_compact(const StepShape& shape, const CompactBuffers& buf, const StepParams& p, hipStream_t stream);
+// cell_map[j] = first cell of the pairs from `unit` j on (unit: kChunk or
+// kWavePairs; n_chunks * kChunk / unit + 1 entries)
 hipError_t launch_prep(const StepShape& sh, StepControl* ctrl, uint64_t* status, int32_t* pair_off, uint32_t* keys,
-                       int32_t* chunk_cell, const StepParams& p, hipStream_t st);
+                       int32_t* cell_map, int unit, const StepParams& p, hipStream_t st);
 
 hipError_t launch_fused(const StepShape& shape, const FusedBuffers& buf, const StepParams& p, hipStream_t stream);
 // one workgroup per cell (baseline); shape.n_step_blocks = n_cells partials

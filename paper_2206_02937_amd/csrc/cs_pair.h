@@ -98,6 +98,206 @@ __device__ __forceinline__ PairSlot pair_index(bool active, int64_t e0, int64_t 
     return s;
 }
 
+// s_waitcnt immediate that waits for vmcnt 0 only (gfx9 encoding: vmcnt in
+// bits 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 at their maxima).
+constexpr int kWaitVmcnt0 = 0x0F70;
+
+// Read-only data at a wave-uniform index through the constant address space,
+// so that the read is one scalar load (the data do not change while the
+// kernel runs).
+template <typename X>
+__device__ __forceinline__ X ld_uniform(const X* p, int64_t i) {
+    return ((const __attribute__((address_space(4))) X*)p)[i];
+}
+
+// The pairing of a wave of 64 consecutive pairs.  (Args: off_e, off_g,
+// pair_off, keys as the scan kernel left them.)
+
+// A cell as the pairing needs it (its ranges start below 2^31).
+struct CellMeta {
+    int32_t e0, g0;
+    uint32_t ne, ng;
+    FeistelKey key;
+    int32_t po;  // its first pair
+};
+
+__device__ __forceinline__ uint32_t larger(const CellMeta& m) { return m.ne > m.ng ? m.ne : m.ng; }
+
+// Cell c's metadata by scalar loads (c wave-uniform).
+template <typename Args>
+__device__ __forceinline__ CellMeta cell_meta(const Args& a, int c) {
+    CellMeta m;
+    const int64_t e0 = ld_uniform(a.off_e, c), g0 = ld_uniform(a.off_g, c);
+    m.e0 = (int32_t)e0;
+    m.g0 = (int32_t)g0;
+    m.ne = (uint32_t)(ld_uniform(a.off_e, c + 1) - e0);
+    m.ng = (uint32_t)(ld_uniform(a.off_g, c + 1) - g0);
+    m.key.k[0] = ld_uniform(a.keys, 4 * (int64_t)c);
+    m.key.k[1] = ld_uniform(a.keys, 4 * (int64_t)c + 1);
+    m.key.k[2] = ld_uniform(a.keys, 4 * (int64_t)c + 2);
+    m.key.k[3] = ld_uniform(a.keys, 4 * (int64_t)c + 3);
+    m.key.bits = ceil_log2(larger(m));
+    m.po = ld_uniform(a.pair_off, c);
+    return m;
+}
+
+// b in the lanes with take set, else a.
+__device__ __forceinline__ CellMeta pick(bool take, const CellMeta& a, const CellMeta& b) {
+    CellMeta m;
+    m.e0 = take ? b.e0 : a.e0;
+    m.g0 = take ? b.g0 : a.g0;
+    m.ne = take ? b.ne : a.ne;
+    m.ng = take ? b.ng : a.ng;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) m.key.k[r] = take ? b.key.k[r] : a.key.k[r];
+    m.key.bits = take ? b.key.bits : a.key.bits;
+    m.po = take ? b.po : a.po;
+    return m;
+}
+
+// Pair i of cell m with the larger species' index v.
+__device__ __forceinline__ PairSlot slot_of(bool act, const CellMeta& m, uint32_t i, uint32_t v) {
+    const bool e_first = m.ne <= m.ng;
+    PairSlot s;
+    s.M = larger(m);
+    s.active = act;
+    s.ie = act ? m.e0 + (int32_t)(e_first ? i : v) : 0;
+    s.ig = act ? m.g0 + (int32_t)(e_first ? v : i) : 0;
+    return s;
+}
+
+// The pairing of a wave whose pairs lie in cell a, or (TWO) in the cells a
+// and b (in_b: the lane's pair is b's).  The cycle-walk of a lane leaves
+// [0, M) for points of [M, 2^b) only: when the wave's cells have at most 64 of
+// those together, one lane each evaluates them, and the walk is a chain of
+// lane reads instead of passes through the network that the wave repeats
+// until its last lane is done (five on average for 64-pair cells: on the uneven
+// plasma, whose pair kernel took 84.0 us, the pairing was 32 us of it).
+template <bool TWO>
+__device__ __forceinline__ PairSlot pair_wave(bool act, uint32_t t, const CellMeta& a, const CellMeta& b, bool in_b) {
+    const CellMeta m = TWO ? pick(in_b, a, b) : a;
+    const uint32_t M = larger(m);
+    const uint32_t i = act ? t - (uint32_t)m.po : 0u;
+    uint32_t v = feistel(i, m.key);
+    const uint64_t act_m = lanes(act);
+    uint64_t out_m = act_m & lanes(v >= M);
+    if (out_m) {
+        const uint32_t n_a = (1u << a.key.bits) - larger(a), n_b = TWO ? (1u << b.key.bits) - larger(b) : 0u;
+        if (n_a + n_b <= 64u && n_a <= 64u) {
+            const uint32_t l = (uint32_t)lane_id();
+            const bool tab_b = TWO && l >= n_a;
+            uint32_t o;
+            if (TWO) {
+                FeistelKey k;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) k.k[r] = tab_b ? b.key.k[r] : a.key.k[r];
+                k.bits = tab_b ? b.key.bits : a.key.bits;
+                o = feistel(tab_b ? larger(b) + (l - n_a) : larger(a) + l, k);
+            } else {
+                o = feistel(larger(a) + l, a.key);
+            }
+            // entry of point v: v - M, after a's entries for b
+            const uint32_t base = M - (TWO && in_b ? n_a : 0u);
+            do {
+                const uint32_t w = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((v - base) << 2), (int)o);
+                v = v >= M ? w : v;  // (an inactive lane's value is not used)
+                out_m = act_m & lanes(v >= M);
+            } while (out_m);
+        } else {
+            bool out = act && v >= M;
+            while (out) {
+                v = feistel(v, m.key);
+                out = v >= M;
+            }
+        }
+    }
+    return slot_of(act, m, i, v);
+}
+
+// The pairing of one lane whose wave's pairs lie in more than two cells, ma
+// (cell cs0) to cell ch.
+template <typename Args>
+__device__ __forceinline__ PairSlot pair_cells(const Args& a, bool act, int32_t t, const CellMeta& ma, int cs0, int ch,
+                                               int32_t po_next) {
+    const int nc = ch - cs0 + 1;
+    CellMeta m = ma;
+    if (nc <= 64) {
+        // lane l reads cell cs0 + l's metadata (one coalesced round trip);
+        // each lane finds its cell among them by a binary search over the
+        // wave's pair offsets and takes that cell's values by lane shuffles
+        const int cl = cs0 + (lane_id() < nc ? lane_id() : nc - 1);
+        const int32_t po_l = a.pair_off[cl];
+        const int64_t e0_l = a.off_e[cl], g0_l = a.off_g[cl];
+        const int32_t ne_l = (int32_t)(a.off_e[cl + 1] - e0_l), ng_l = (int32_t)(a.off_g[cl + 1] - g0_l);
+        const uint4 key_l = *(const uint4*)(a.keys + 4 * (int64_t)cl);
+        int lo = 0, hi = nc - 1;
+#pragma unroll
+        for (int it = 0; it < 6; ++it) {  // nc <= 64 = 2^6
+            const int mid = (lo + hi + 1) >> 1;
+            if (__shfl(po_l, mid, 64) <= t)
+                lo = mid;
+            else
+                hi = mid - 1;
+        }
+        // (shuffles by the whole wave)
+        m.e0 = __shfl((int32_t)e0_l, lo, 64);
+        m.g0 = __shfl((int32_t)g0_l, lo, 64);
+        m.ne = (uint32_t)__shfl(ne_l, lo, 64);
+        m.ng = (uint32_t)__shfl(ng_l, lo, 64);
+        m.key.k[0] = __shfl(key_l.x, lo, 64);
+        m.key.k[1] = __shfl(key_l.y, lo, 64);
+        m.key.k[2] = __shfl(key_l.z, lo, 64);
+        m.key.k[3] = __shfl(key_l.w, lo, 64);
+        m.po = __shfl(po_l, lo, 64);
+        m.key.bits = ceil_log2(larger(m));
+    } else if (act && t >= po_next) {
+        // more than 64 cells: a binary search per lane
+        int lo = cs0 + 1, hi = ch;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (a.pair_off[mid] <= t)
+                lo = mid;
+            else
+                hi = mid - 1;
+        }
+        const int64_t e0 = a.off_e[lo], g0 = a.off_g[lo];
+        const uint4 key = *(const uint4*)(a.keys + 4 * (int64_t)lo);
+        m.e0 = (int32_t)e0;
+        m.g0 = (int32_t)g0;
+        m.ne = (uint32_t)(a.off_e[lo + 1] - e0);
+        m.ng = (uint32_t)(a.off_g[lo + 1] - g0);
+        m.key.k[0] = key.x;
+        m.key.k[1] = key.y;
+        m.key.k[2] = key.z;
+        m.key.k[3] = key.w;
+        m.po = a.pair_off[lo];
+        m.key.bits = ceil_log2(larger(m));
+    }
+    // complete these reads inside the branch, so that no read of it is still
+    // counted as possibly in flight after it (which would make later waits
+    // include the particle reads)
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    const uint32_t i = act ? (uint32_t)(t - m.po) : 0u;
+    return slot_of(act, m, i, act ? shuffle_index(i, larger(m), m.key) : 0u);
+}
+
+// The wave's pairs t_wave .. t_wave + 63 below T_total, lane by lane; cs0 is
+// the cell of the first, ch that of the last or a later one.  They lie in one
+// cell, in two, or in more: the metadata of up to two cells come by scalar
+// loads (with 64-pair cells 95 % of the waves; one lane per cell and a search
+// by lane reads for all that spanned two, before).
+template <typename Args>
+__device__ __forceinline__ PairSlot pair_slots(const Args& a, int32_t t_wave, int32_t T_total, int cs0, int ch) {
+    const int32_t t = t_wave + lane_id();
+    const bool act = t < T_total;
+    const CellMeta ma = cell_meta(a, cs0);
+    const int32_t po_next = ld_uniform(a.pair_off, cs0 + 1);
+    const int32_t t_last = t_wave + 63 < T_total ? t_wave + 63 : T_total - 1;
+    if (t_last < po_next) return pair_wave<false>(act, (uint32_t)t, ma, ma, false);
+    if (ch == cs0 + 1) return pair_wave<true>(act, (uint32_t)t, ma, cell_meta(a, ch), t >= po_next);
+    return pair_cells(a, act, t, ma, cs0, ch, po_next);
+}
+
 template <typename T>
 __device__ __forceinline__ PairRaw<T> pair_load(const Particles<T>& a, const PairSlot& s) {
     PairRaw<T> r;
@@ -129,7 +329,10 @@ template <typename T, bool O32 = false>
 __device__ __forceinline__ PairRaw<T> pair_load_all(const Particles<T>& a, const PairSlot& s) {
     PairRaw<T> r;
     if constexpr (O32) {
-        const uint32_t oe = (uint32_t)s.ie * (uint32_t)sizeof(T), og = (uint32_t)s.ig * (uint32_t)sizeof(T);
+        uint32_t oe = (uint32_t)s.ie * (uint32_t)sizeof(T), og = (uint32_t)s.ig * (uint32_t)sizeof(T);
+        // (opaque here, so that the offsets are not widened before they reach
+        // the loads and the bases stay in scalar registers)
+        asm("" : "+v"(oe), "+v"(og));
         auto at = [](const T* b, uint32_t o) { return *(const T*)((const char*)b + (uint64_t)o); };
         r.p[0] = at(a.ex, oe);
         r.p[1] = at(a.ey, oe);
@@ -152,49 +355,51 @@ __device__ __forceinline__ PairRaw<T> pair_load_all(const Particles<T>& a, const
     return r;
 }
 
+// A weight the pair can use: finite and not negative.
+__device__ __forceinline__ bool weight_ok(float w) { return __builtin_isfpclass(w, 0x1E0); }
+__device__ __forceinline__ bool weight_ok(double w) { return __builtin_isfpclass(w, 0x1E0); }
+
 // `sig_tab`: kSigTab or a copy of it (see sigma_ratio_tab).
+//
+// Every lane evaluates every step, and what an inactive or invalid lane gets
+// is replaced at the end: kept in branches of their own, the steps cost the
+// initial values and selects of everything they define (292 vector
+// instructions per 64 pairs for the whole pair kernel, 244 now).  (1 + p.p) k.k in
+// [1e-300, 1e300] implies finite momenta, so one range test per lane stands
+// for the six finiteness tests and for x_flux's own; a wave with an active
+// lane outside it (or with an unusable weight) takes the general form, whose
+// result for the other lanes is the same bit for bit.
 template <typename T>
 __device__ __forceinline__ PairOutcome pair_physics(const PairSlot& s, const PairRaw<T>& r, double dt,
                                                     double density_norm, uint64_t seed, uint64_t step,
                                                     const double* sig_tab = kSigTab) {
+    const d3 p = {(double)r.p[0], (double)r.p[1], (double)r.p[2]};
+    const d3 k = {(double)r.k[0], (double)r.k[1], (double)r.k[2]};
+    const double pp = dot(p, p), kk = dot(k, k);
+    const double a = (1.0 + pp) * kk;
+    const uint64_t plain =
+        lanes(weight_ok(r.we)) & lanes(weight_ok(r.wg)) & lanes(a >= kFluxNormalMin) & lanes(a <= kFluxNormalMax);
+    bool valid = s.active;
+    XFlux xf;
+    if ((lanes(s.active) & ~plain) == 0) {
+        xf = x_flux_impl<true>(p, k, pp, kk);
+    } else {
+        valid = s.active && finite_pair(p, (double)r.we, k, (double)r.wg);
+        xf = valid ? x_flux(p, k, pp, kk) : XFlux{0.0, 0.0};
+    }
+    const double wmax = (double)(r.we > r.wg ? r.we : r.wg);
+    const double tau = dt * density_norm * (double)s.M;
+    double P = tau * wmax * sigma_ratio_tab(xf.x, sig_tab) * xf.flux;
+    P = valid && xf.x > 0.0 ? P : 0.0;
     PairOutcome o;
     o.ie = s.ie;
     o.ig = s.ig;
-    o.x = 0.0;
-    o.P = 0.0;
-    o.accept = false;
-    o.clipped = false;
-    o.invalid = false;
-    double x = 0.0, flux = 0.0, wmax = 0.0, tau = 0.0;
-    bool compute = false;
-    if (s.active) {
-        const d3 p = {(double)r.p[0], (double)r.p[1], (double)r.p[2]};
-        const d3 k = {(double)r.k[0], (double)r.k[1], (double)r.k[2]};
-        const double we = (double)r.we, wg = (double)r.wg;
-        if (!finite_pair(p, we, k, wg)) {
-            o.invalid = true;
-        } else {
-            const XFlux xf = x_flux(p, k, dot(p, p), dot(k, k));
-            x = xf.x;
-            flux = xf.flux;
-            tau = dt * density_norm * (double)s.M;
-            wmax = we > wg ? we : wg;
-            compute = x > 0.0;
-        }
-    }
-    if (compute) {
-        double P = tau * wmax * sigma_ratio_tab(x, sig_tab) * flux;
-        if (P > 1.0) {
-            o.clipped = true;
-            P = 1.0;
-        }
-        o.P = P;
-    }
-    if (s.active && !o.invalid) {
-        const u32x4 u = draw(seed, (uint64_t)o.ie, step, kCollide);
-        o.accept = uniform53(u.a, u.b) < o.P;
-    }
-    o.x = x;
+    o.x = valid ? xf.x : 0.0;
+    o.clipped = P > 1.0;
+    o.P = o.clipped ? 1.0 : P;
+    o.invalid = s.active && !valid;
+    const u32x4 u = draw(seed, (uint64_t)(uint32_t)s.ie, step, kCollide);
+    o.accept = uniform53(u.a, u.b) < o.P;  // (P = 0 where the pair is not valid)
     return o;
 }
 
@@ -351,7 +556,7 @@ __device__ __forceinline__ void collide_stash(const Particles<T>& a, bool active
 
 // An accepted pair staged in LDS with its particle values.
 template <typename T>
-struct StagedPair {
+struct alignas(8) StagedPair {
     int32_t ie, ig;
     T p[3], k[3], we, wg;
 };
