@@ -167,12 +167,12 @@ CS_API cs_status cs_compton_step(cs_ctx* ctx, cs_dtype dtype, cs_species electro
  * results (bit for bit) and errors as cs_compton_step; it always runs the
  * fused strategy, whatever the context's options.
  *
- * Its workspace is a static device buffer of 8 MiB that the library holds on
- * every device it runs on until the process ends (looked up and initialised
- * once per device by cs_create).  That bounds the problem: about 24 bytes per
- * cell plus 4 per 256 pairs, i.e. roughly 340,000 cells of 256 pairs; larger
- * problems fail with CS_ERR_UNSUPPORTED (and cs_last_error says how much the
- * step would need) before anything is queued.
+ * Its workspace is a static device buffer of 8 MiB (and 28 KiB) that the
+ * library holds on every device it runs on until the process ends (looked up
+ * and initialised once per device by cs_create).  That bounds the problem:
+ * about 24 bytes per cell plus 4 per 256 pairs, i.e. roughly 340,000 cells of
+ * 256 pairs; larger problems fail with CS_ERR_UNSUPPORTED (and cs_last_error
+ * says how much the step would need) before anything is queued.
  *
  * Every call on one device shares that device's buffer, whatever the
  * context: calls on one stream (or otherwise ordered) are safe; calls that

@@ -94,7 +94,9 @@ bool species_ok(const cs_species& s) {
 // is a stand-in, not a device address): cs_create looks up the device address
 // of its copy on each device once, with that device current, and everything
 // after that uses the looked-up address.
-constexpr size_t kStaticScratchBytes = (size_t)8 << 20;
+// (8 MiB, and the partial sums of the workgroups beyond 512 that a step of few
+// chunks can have)
+constexpr size_t kStaticScratchBytes = ((size_t)8 << 20) + 512 * 7 * 8;
 constexpr int64_t kStaticStatusWords = 4096;
 __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kMaxStaticDevices = 64;
@@ -269,12 +271,7 @@ Plan plan_step(int64_t strategy, int64_t chunks_per_block, int64_t pairs_per_lan
     sh.n_collide_blocks = sh.n_chunks < 1024 ? (sh.n_chunks > 0 ? sh.n_chunks : 1) : 1024;
     sh.scan_tmp_len = cs::step_scan_tmp_len(n_cells, sh.n_chunks);
     int64_t G = chunks_per_block;
-    if (G <= 0) {
-        // automatic: about 512 workgroups (2 per compute unit at the fused
-        // kernel's occupancy), at most 16 chunks each
-        G = sh.n_chunks / 512;
-        if (G > 16) G = 16;
-    }
+    if (G <= 0) G = cs::fused_fit_chunks(dtype, sampler, sh.n_chunks);
     if (G < 1) G = 1;
     sh.chunks_per_block = G;
     sh.n_step_blocks = sh.n_chunks > 0 ? (sh.n_chunks + G - 1) / G : 1;

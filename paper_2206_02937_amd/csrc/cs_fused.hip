@@ -7,10 +7,10 @@
 //                256-pair chunk (64-pair wave for the compact strategy).
 //   k_step       persistent over chunks: each workgroup evaluates `chunks`
 //                consecutive 256-pair chunks (pairing, x, s(x), P, accept),
-//                appends accepted pairs in pair order to a queue in LDS, and
-//                drains the queue densely (all lanes busy) whenever it holds
-//                a full workgroup of pairs and at the end; per-workgroup partial
-//                sums go to the workspace.
+//                each wave appends its accepted pairs to a queue in LDS and
+//                drains it densely (all lanes busy) whenever it holds a full
+//                wave of pairs, the workgroup what is left at the end;
+//                per-workgroup partial sums go to the workspace.
 //   k_finalize_step  one workgroup reduces the partial sums in a fixed order
 //                into cs_stats and advances the step epoch and device step.
 //
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep_scan(const PrepArgs a) {
 // ---------------------------------------------------------------------------
 // k_step
 // ---------------------------------------------------------------------------
-constexpr int kQueueCap = 2 * kChunk;  // holds < kChunk before a chunk adds <= kChunk
+constexpr int kWaveCap = 2 * 64;  // a wave's queue: holds < 64 before 64 pairs add at most as many
 
 template <typename T>
 struct FusedArgs {
@@ -154,157 +154,218 @@ struct FusedArgs {
     MlpDev mlp;  // network samplers only
 };
 
-// Resolve the n staged pairs at queue[0..n): the plain sampler, or the
-// network (every entry of this stack lies in the network's domain).
-template <typename T, int SAMP>
-__device__ void drain(const FusedArgs<T>& a, const StagedPair<T>* queue, int n, uint64_t step, NetLds<SAMP>& s_net,
-                      CollideSums& sums) {
-    for (int base = 0; base < n; base += kChunk) {
-        const int q = base + (int)threadIdx.x;
-        // waves with no item skip the pass entirely
-        if (__any(q < n)) {
-            const bool active = q < n;
-            const StagedPair<T>* e = queue + (active ? q : 0);
-            if constexpr (SAMP == CS_SAMPLER_PLAIN)
-                collide_staged<T>(a.pt, active, e, a.seed, step, sums);
-            else
-                collide_net<T, SAMP>(a.pt, active, FromStaged<T>{e}, s_net, a.mlp, a.seed, step, sums);
-        }
-    }
+// LDS written by lanes of a wave is read by others of it from here on (a
+// wave's LDS accesses complete in order).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Network samplers: the n pairs outside the network's domain, staged from
-// the top of the queue down (queue[cap - 1 - q]), go to the plain sampler in
-// dense passes.
+// The wave's step over its lanes' staged pairs e (`active` in at least one
+// lane): the plain sampler, or the network (every pair of the main stack lies
+// in the network's domain).
+template <typename T, int SAMP>
+__device__ __forceinline__ void drain(const FusedArgs<T>& a, bool active, const StagedPair<T>* e, uint64_t step,
+                                      NetLds<SAMP>& s_net, CollideSums& sums) {
+    if constexpr (SAMP == CS_SAMPLER_PLAIN)
+        collide_staged<T>(a.pt, active, e, a.seed, step, sums);
+    else
+        collide_net<T, SAMP>(a.pt, active, FromStaged<T>{e}, s_net, a.mlp, a.seed, step, sums);
+}
+
+// Network samplers: staged pairs outside the network's domain, with the
+// plain sampler.
 template <typename T>
-__device__ void drain_fallback(const FusedArgs<T>& a, const StagedPair<T>* queue, int n, uint64_t step,
-                               CollideSums& sums) {
-    for (int base = 0; base < n; base += kChunk) {
-        const int q = base + (int)threadIdx.x;
-        if (__any(q < n)) {
-            const bool active = q < n;
-            collide_staged<T>(a.pt, active, queue + (kQueueCap - 1 - (active ? q : 0)), a.seed, step, sums);
-            sums.n_fallback += active ? 1 : 0;
-        }
-    }
+__device__ __forceinline__ void drain_fallback(const FusedArgs<T>& a, bool active, const StagedPair<T>* e,
+                                               uint64_t step, CollideSums& sums) {
+    collide_staged<T>(a.pt, active, e, a.seed, step, sums);
+    sums.n_fallback += active ? 1 : 0;
 }
 
-template <typename T, int SAMP>
-__global__ __launch_bounds__(kChunk) void k_step(const FusedArgs<T> a) {
-    __shared__ StagedPair<T> s_queue[kQueueCap];
+// The pairing and the particle reads of the wave's pairs of one chunk, cells
+// c_lo (of the chunk's first pair) to c_hi: the first and the last cell of
+// the wave's own 64 pairs come from one coalesced read of the chunk's pair
+// offsets and two votes.
+template <typename T, bool O32>
+__device__ __forceinline__ void step_fetch(const FusedArgs<T>& a, int32_t t_wave, int32_t T_total, int c_lo, int c_hi,
+                                           PairSlot& sl, PairRaw<T>& raw) {
+    sl = PairSlot{0, 0, 0, false};
+    if (t_wave < T_total) {  // uniform
+        const int nc = c_hi - c_lo + 1;
+        if (nc > 1 && nc <= 64) {
+            const int l = lane_id() < nc ? lane_id() : nc - 1;
+            const int32_t po = a.pair_off[c_lo + l];
+            const int32_t t_last = t_wave + 63 < T_total ? t_wave + 63 : T_total - 1;
+            const uint64_t in = ~0ull >> (64 - nc);
+            c_hi = c_lo + __popcll(lanes(po <= t_last) & in) - 1;
+            c_lo += __popcll(lanes(po <= t_wave) & in) - 1;
+        }
+        sl = pair_slots(a, t_wave, T_total, c_lo, c_hi);
+    }
+    raw = pair_load_all<T, O32>(a.pt, sl);
+}
+
+// Each wave takes its 64 pairs of every chunk and keeps its own queue, so
+// that no wave waits for another until the end.  The pairing and the particle
+// reads of a chunk are issued before the physics of the one before it, which
+// reads nothing from global memory (the s(x) table is in LDS).  Bound by the
+// vector instructions of the pairs and of the sampler.  FP32 storage, plain
+// sampler, against one queue per workgroup, three barriers per chunk and
+// nothing read ahead: 2^22 pairs in 256-pair cells 119.8 -> 63.4 us, in
+// 64-pair cells of uneven filling 168 -> 95 us, 2^20 pairs 41.1 -> 25.7 us,
+// 2^24 pairs 416 -> 258 us; FP64 storage 142.9 -> 83.2 us at 2^22 pairs; BF16
+// network 139 -> 98 us.  With the plain sampler on FP32 storage four waves
+// per SIMD are asked for (126 registers; the 143 it takes by itself allow
+// three: 76 us where four take 62; five, with spills, 75).
+template <typename T, int SAMP, bool O32>
+__global__ __launch_bounds__(kChunk, SAMP == CS_SAMPLER_PLAIN && sizeof(T) == 4 ? 4 : 1) void k_step(
+    const FusedArgs<T> args) {
+    __shared__ double s_sig[kSigTabSegments * kSigTabTerms];
+    __shared__ StagedPair<T> s_queue[kChunk / 64][kWaveCap];
     __shared__ NetLds<SAMP> s_net;
-    __shared__ int s_wcnt[2][kChunk / 64];
-    __shared__ int s_qn, s_qf;
+    __shared__ int s_left[2][kChunk / 64];
     __shared__ double s_red_d[3 * (kChunk / 64)];
     __shared__ long long s_red_i[4 * (kChunk / 64)];
+    constexpr bool NET = SAMP != CS_SAMPLER_PLAIN;
+    // The arguments by scalar loads where they are used: `own` makes their
+    // address opaque, so that they are not held in scalar registers from one
+    // use to the next (there are too few for the sampler's constants as well,
+    // and what does not fit is kept in lanes of vector registers).
+    const auto own = [] {
+        auto p = (const __attribute__((address_space(4))) FusedArgs<T>*)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(p));
+        return (const FusedArgs<T>*)p;
+    };
+    (void)args;  // (the kernel's only argument: at the segment's start)
+    const FusedArgs<T>& a = *own();
     const int tid = threadIdx.x;
     const int lane = lane_id();
-    const int wave = tid >> 6;
+    const int wave = wave_uniform(tid >> 6);
+    for (int i = tid; i < kSigTabSegments * kSigTabTerms; i += kChunk) s_sig[i] = kSigTab[i];
     StepControl* ctrl = a.ctrl;
+    const int32_t T_read = a.pair_off[a.n_cells];
     const CtrlView cv = ctrl_view(ctrl);
-    const uint32_t E = cv.epoch;
     const uint64_t step = cv.step;
-    const bool layout_ok = cv.layout_ok;
     double sum_p = 0.0;
-    long long n_clip = 0, n_inv = 0, n_coll = 0;
+    long long n_clip = 0, n_inv = 0, n_coll = 0;  // wave-uniform
     CollideSums sums;
-    if (tid == 0) s_qn = s_qf = 0;
     net_load<SAMP>(s_net, a.mlp);
+    // (no pair at all under a layout error; reads past the map then too)
+    const int32_t T_total = cv.layout_ok ? T_read : 0;
+    const int64_t n_used = ((int64_t)T_total + kChunk - 1) / kChunk;
+    const int64_t j_begin = (int64_t)blockIdx.x * a.chunks_per_block;
+    int64_t j_end = j_begin + a.chunks_per_block;
+    if (j_end > a.n_chunks) j_end = a.n_chunks;
+    if (j_end > n_used) j_end = n_used;
+    // two stacks in the wave's queue: from the bottom, and (network samplers,
+    // x outside the network's domain) from the top
+    StagedPair<T>* queue = s_queue[wave];
+    int qn = 0, qf = 0;  // wave-uniform
+    const uint64_t lanes_below = (1ull << lane) - 1ull;
     __syncthreads();
-    if (layout_ok) {
-        const int32_t T_total = a.pair_off[a.n_cells];
-        const int64_t j_begin = (int64_t)blockIdx.x * a.chunks_per_block;
-        int64_t j_end = j_begin + a.chunks_per_block;
-        if (j_end > a.n_chunks) j_end = a.n_chunks;
-        for (int64_t j = j_begin; j < j_end; ++j) {
-            if (j * kChunk >= T_total) break;  // uniform over the block
-            const int32_t t = (int32_t)(j * kChunk) + tid;
-            const bool active = t < T_total;
-            int c = 0;
-            if (active) {
-                int lo = a.chunk_cell[j], hi = a.chunk_cell[j + 1];
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (a.pair_off[mid] <= t)
-                        lo = mid;
-                    else
-                        hi = mid - 1;
-                }
-                c = lo;
+    PairSlot sl = {0, 0, 0, false};
+    PairRaw<T> raw = {};
+    int c_next = 0;
+    if (j_begin < j_end) {
+        c_next = ld_uniform(a.chunk_cell, j_begin + 1);
+        step_fetch<T, O32>(a, (int32_t)(j_begin * kChunk) + 64 * wave, T_total, ld_uniform(a.chunk_cell, j_begin),
+                           c_next, sl, raw);
+    }
+    for (int64_t j = j_begin;; ++j) {
+        const FusedArgs<T>& a = *own();
+        const bool last = j >= j_end;  // uniform over the block
+        // the entries to resolve now: n_main of the main stack (lane q's at
+        // e_main), n_fb of the other (the waves' leftovers in the last round)
+        const StagedPair<T>*e_main = queue, *e_fb = queue;
+        uint64_t main_m = 0, fb_m = 0;  // lanes with an entry
+        if (!last) {
+            const PairSlot s = sl;
+            const PairRaw<T> r = raw;
+            if (j + 1 < j_end) {
+                const int c_lo = c_next;
+                c_next = ld_uniform(a.chunk_cell, j + 2);
+                step_fetch<T, O32>(a, (int32_t)((j + 1) * kChunk) + 64 * wave, T_total, c_lo, c_next, sl, raw);
             }
-            const PairOutcome o = pair_eval<T>(a.pt, active, a.off_e[c], a.off_e[c + 1], a.off_g[c], a.off_g[c + 1],
-                                               a.keys + 4 * c, (uint32_t)(t - (active ? a.pair_off[c] : 0)), a.dt,
-                                               a.density_norm, a.seed, step);
+            const PairOutcome o = pair_physics<T>(s, r, a.dt, a.density_norm, a.seed, step, s_sig);
             sum_p += o.P;
-            n_clip += o.clipped ? 1 : 0;
-            n_inv += o.invalid ? 1 : 0;
-            // accepted pairs are staged in LDS: from the bottom of the queue,
-            // or (network samplers, x outside the network's domain) from the top
+            n_clip += __popcll(lanes(o.clipped));
+            n_inv += __popcll(lanes(o.invalid));
             bool to_fb = false;
-            if constexpr (SAMP != CS_SAMPLER_PLAIN) to_fb = o.accept && !in_range((float)o.x, a.mlp.dom);
-            const bool to_main = o.accept && !to_fb;
-            const uint64_t lt = (1ull << lane) - 1ull;
-            const uint64_t mask = __ballot(to_main), mask_fb = __ballot(to_fb);
-            const int before = __popcll(mask & lt), before_fb = __popcll(mask_fb & lt);
-            if (lane == 0) {
-                s_wcnt[0][wave] = __popcll(mask);
-                s_wcnt[1][wave] = __popcll(mask_fb);
-            }
-            __syncthreads();
-            int wbase = 0, total = 0, wbase_fb = 0, total_fb = 0;
-#pragma unroll
-            for (int w = 0; w < kChunk / 64; ++w) {
-                wbase += w < wave ? s_wcnt[0][w] : 0;
-                total += s_wcnt[0][w];
-                wbase_fb += w < wave ? s_wcnt[1][w] : 0;
-                total_fb += s_wcnt[1][w];
-            }
-            const int qn = s_qn, qf = s_qf;
+            if constexpr (NET) to_fb = o.accept && !in_range((float)o.x, a.mlp.dom);
+            const uint64_t acc = lanes(o.accept), mask_fb = NET ? lanes(to_fb) : 0, mask = acc & ~mask_fb;
+            n_coll += __popcll(acc);
             if (o.accept) {
-                StagedPair<T>& e = to_fb ? s_queue[kQueueCap - 1 - (qf + wbase_fb + before_fb)]
-                                         : s_queue[qn + wbase + before];
-                e.ie = o.ie;
-                e.ig = o.ig;
-                e.p[0] = a.pt.ex[o.ie];
-                e.p[1] = a.pt.ey[o.ie];
-                e.p[2] = a.pt.ez[o.ie];
-                e.k[0] = a.pt.gx[o.ig];
-                e.k[1] = a.pt.gy[o.ig];
-                e.k[2] = a.pt.gz[o.ig];
-                e.we = a.pt.ew[o.ie];
-                e.wg = a.pt.gw[o.ig];
+                StagedPair<T>& e = to_fb ? queue[kWaveCap - 1 - (qf + __popcll(mask_fb & lanes_below))]
+                                         : queue[qn + __popcll(mask & lanes_below)];
+                e.ie = s.ie;
+                e.ig = s.ig;
+                e.p[0] = r.p[0];
+                e.p[1] = r.p[1];
+                e.p[2] = r.p[2];
+                e.k[0] = r.k[0];
+                e.k[1] = r.k[1];
+                e.k[2] = r.k[2];
+                e.we = r.we;
+                e.wg = r.wg;
             }
-            n_coll += o.accept ? 1 : 0;
-            __syncthreads();
-            // both stacks hold < kChunk entries together before a chunk adds
-            // at most kChunk, so they never meet (kQueueCap = 2 kChunk)
-            if (qn + total + qf + total_fb >= kChunk) {
-                drain<T, SAMP>(a, s_queue, qn + total, step, s_net, sums);
-                if constexpr (SAMP != CS_SAMPLER_PLAIN) drain_fallback<T>(a, s_queue, qf + total_fb, step, sums);
-                __syncthreads();
-                if (tid == 0) s_qn = s_qf = 0;
-            } else if (tid == 0) {
-                s_qn = qn + total;
-                s_qf = qf + total_fb;
+            qn += __popcll(mask);
+            qf += __popcll(mask_fb);
+            if (qn + qf < 64) continue;
+            // both stacks hold < 64 entries together before 64 pairs add at
+            // most 64, so they never meet; a stack of 64 or more gives its top
+            // 64, and where neither has as many both give all they have
+            if (qn >= 64 || qf < 64) {
+                const int n = qn < 64 ? qn : 64;
+                qn -= n;
+                main_m = n > 0 ? ~0ull >> (64 - n) : 0;
+                e_main = queue + qn + (lane < n ? lane : 0);
+            }
+            if (NET && qf > 0 && (qf >= 64 || qn == 0)) {
+                const int n = qf < 64 ? qf : 64;
+                qf -= n;
+                fb_m = ~0ull >> (64 - n);
+                e_fb = queue + (kWaveCap - 1 - qf - (lane < n ? lane : 0));
+            }
+            wave_lds_sync();
+        } else {
+            // what the waves have left (fewer than 64 each), together: lane q
+            // of the workgroup takes entry q
+            if (lane == 0) {
+                s_left[0][wave] = qn;
+                s_left[1][wave] = qf;
             }
             __syncthreads();
+            int w = 0, q = tid, w_fb = 0, q_fb = tid;
+#pragma unroll
+            for (int i = 0; i < kChunk / 64 - 1; ++i) {
+                const int l = s_left[0][i], l_fb = s_left[1][i];
+                if (w == i && q >= l) ++w, q -= l;
+                if (w_fb == i && q_fb >= l_fb) ++w_fb, q_fb -= l_fb;
+            }
+            const bool in = q < s_left[0][w], in_fb = q_fb < s_left[1][w_fb];
+            main_m = lanes(in);
+            fb_m = lanes(in_fb);
+            e_main = &s_queue[w][in ? q : 0];
+            e_fb = &s_queue[w_fb][kWaveCap - 1 - (in_fb ? q_fb : 0)];
         }
-        const int qn = s_qn, qf = s_qf;
-        if (qn > 0) drain<T, SAMP>(a, s_queue, qn, step, s_net, sums);
-        if constexpr (SAMP != CS_SAMPLER_PLAIN)
-            if (qf > 0) drain_fallback<T>(a, s_queue, qf, step, sums);
+        const FusedArgs<T>& ad = *own();
+        if (main_m) drain<T, SAMP>(ad, main_m >> lane & 1, e_main, step, s_net, sums);
+        if constexpr (NET)
+            if (fb_m) drain_fallback<T>(ad, fb_m >> lane & 1, e_fb, step, sums);
+        if (last) break;
+        wave_lds_sync();
     }
     // per-workgroup partials, fixed order: lanes (butterfly), then waves
     const double w_p = wave_sum(sum_p), w_eb = wave_sum(sums.e_before), w_ea = wave_sum(sums.e_after);
-    const long long w_cl = wave_sum_i(n_clip), w_in = wave_sum_i(n_inv), w_co = wave_sum_i(n_coll);
-    const long long w_fb = wave_sum_i(sums.n_fallback);
+    const long long w_fb = NET ? wave_sum_i(sums.n_fallback) : 0;
     if (lane == 0) {
         s_red_d[3 * wave + 0] = w_p;
         s_red_d[3 * wave + 1] = w_eb;
         s_red_d[3 * wave + 2] = w_ea;
-        s_red_i[4 * wave + 0] = w_cl;
-        s_red_i[4 * wave + 1] = w_in;
-        s_red_i[4 * wave + 2] = w_co;
+        s_red_i[4 * wave + 0] = n_clip;
+        s_red_i[4 * wave + 1] = n_inv;
+        s_red_i[4 * wave + 2] = n_coll;
         s_red_i[4 * wave + 3] = w_fb;
     }
     __syncthreads();
@@ -438,12 +499,20 @@ int64_t fused_prep_blocks(int64_t n_cells) { return (n_cells + kPrepCells - 1) /
 
 static size_t al(size_t v) { return (v + 255) & ~(size_t)255; }
 
+// Entries of each partial-sum array: the workgroups, and room for 16 chunks
+// each at least (what a step needs of a bounded workspace does not depend on
+// the split).
+static int64_t fused_part_len(const StepShape& s) {
+    const int64_t n = (s.n_chunks + 15) / 16;
+    return s.n_step_blocks > n ? s.n_step_blocks : n;
+}
+
 size_t fused_workspace_bytes(const StepShape& s) {
     size_t b = 0;
     b += al(sizeof(int32_t) * (s.n_cells + 1));
     b += al(sizeof(uint32_t) * 4 * (s.n_cells > 0 ? s.n_cells : 1));
     b += al(sizeof(int32_t) * (s.n_chunks + 1));
-    b += 7 * al(8 * s.n_step_blocks);
+    b += 7 * al(8 * fused_part_len(s));
     return b;
 }
 
@@ -459,13 +528,13 @@ void carve_fused_buffers(const Workspace& w, const StepShape& s, FusedBuffers* b
     b->pair_off = (int32_t*)take(sizeof(int32_t) * (s.n_cells + 1));
     b->cell_keys = (uint32_t*)take(sizeof(uint32_t) * 4 * (s.n_cells > 0 ? s.n_cells : 1));
     b->chunk_cell = (int32_t*)take(sizeof(int32_t) * (s.n_chunks + 1));
-    b->part.prob = (double*)take(8 * s.n_step_blocks);
-    b->part.e_before = (double*)take(8 * s.n_step_blocks);
-    b->part.e_after = (double*)take(8 * s.n_step_blocks);
-    b->part.clipped = (int64_t*)take(8 * s.n_step_blocks);
-    b->part.invalid = (int64_t*)take(8 * s.n_step_blocks);
-    b->part.collided = (int64_t*)take(8 * s.n_step_blocks);
-    b->part.fallback = (int64_t*)take(8 * s.n_step_blocks);
+    b->part.prob = (double*)take(8 * fused_part_len(s));
+    b->part.e_before = (double*)take(8 * fused_part_len(s));
+    b->part.e_after = (double*)take(8 * fused_part_len(s));
+    b->part.clipped = (int64_t*)take(8 * fused_part_len(s));
+    b->part.invalid = (int64_t*)take(8 * fused_part_len(s));
+    b->part.collided = (int64_t*)take(8 * fused_part_len(s));
+    b->part.fallback = (int64_t*)take(8 * fused_part_len(s));
 }
 
 hipError_t launch_prep(const StepShape& sh, StepControl* ctrl, uint64_t* status, int32_t* pair_off, uint32_t* keys,
@@ -489,6 +558,53 @@ hipError_t launch_prep(const StepShape& sh, StepControl* ctrl, uint64_t* status,
     pa.ctrl = ctrl;
     k_prep_scan<<<(unsigned)fused_prep_blocks(sh.n_cells), kPrepThreads, 0, st>>>(pa);
     return hipGetLastError();
+}
+
+// Workgroups of k_step<T, SAMP, true> resident at once on the current device,
+// at most kFusedMaxBlocks (what the partial sums of a small step have room
+// for), computed once.
+constexpr int64_t kFusedMaxBlocks = 1024;
+
+template <typename T, int SAMP>
+static int64_t step_resident_blocks() {
+    static int64_t cached = -1;
+    if (cached < 0) {
+        int dev = 0, n_cu = 0, per_cu = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &per_cu, reinterpret_cast<const void*>(&k_step<T, SAMP, true>), kChunk, 0) != hipSuccess ||
+            n_cu <= 0 || per_cu <= 0)
+            return 512;  // unknown
+        const int64_t n = (int64_t)n_cu * per_cu;
+        cached = n < kFusedMaxBlocks ? n : kFusedMaxBlocks;
+    }
+    return cached;
+}
+
+template <typename T>
+static int64_t step_resident_blocks(cs_sampler sampler) {
+    switch (sampler) {
+        case CS_SAMPLER_MLP_F32:
+            return step_resident_blocks<T, CS_SAMPLER_MLP_F32>();
+        case CS_SAMPLER_MLP_BF16:
+            return step_resident_blocks<T, CS_SAMPLER_MLP_BF16>();
+        case CS_SAMPLER_MLP_FP8:
+            return step_resident_blocks<T, CS_SAMPLER_MLP_FP8>();
+        default:
+            return step_resident_blocks<T, CS_SAMPLER_PLAIN>();
+    }
+}
+
+// One round of resident workgroups, at most 32 chunks each.  Plain sampler,
+// FP32 storage (1024 resident): 4096 chunks take 26.1 us at 4 each and 29.5 at
+// 8; 16384 chunks 62.2 at 16, 68.4 at 8, 73.7 at 24.  Beyond 32 the rounds
+// stop counting (65536 chunks: 266 us at 16, 255 at 32, 251 at 64).
+int64_t fused_fit_chunks(cs_dtype dtype, cs_sampler sampler, int64_t n_chunks) {
+    const int64_t r = dtype == CS_F64 ? step_resident_blocks<double>(sampler) : step_resident_blocks<float>(sampler);
+    int64_t g = (n_chunks + r - 1) / r;
+    if (g > 32) g = 32;
+    return g < 1 ? 1 : g;
 }
 
 template <typename T, int SAMP>
@@ -517,7 +633,12 @@ static hipError_t launch_fused_t(const StepShape& sh, const FusedBuffers& b, con
     fa.part = b.part;
     fa.stats = p.stats;
     fa.mlp = p.net;
-    k_step<T, SAMP><<<(unsigned)sh.n_step_blocks, kChunk, 0, st>>>(fa);
+    // 32-bit byte offsets whenever both species fit them (see pair_load_all)
+    constexpr int64_t kO32Max = ((int64_t)1 << 32) / (int64_t)sizeof(T);
+    if (!p.wide_index && sh.ne <= kO32Max && sh.ng <= kO32Max)
+        k_step<T, SAMP, true><<<(unsigned)sh.n_step_blocks, kChunk, 0, st>>>(fa);
+    else
+        k_step<T, SAMP, false><<<(unsigned)sh.n_step_blocks, kChunk, 0, st>>>(fa);
     mark(2);
     mark(3);
     mark(4);

@@ -127,6 +127,8 @@ int64_t compact_collide_threads(cs_sampler s);
 // to be resident at once on the current device
 int64_t compact_fit_chunks(cs_dtype dtype, int64_t ppl, int64_t n_chunks);
 int64_t compact_pair_blocks(const StepShape& s);
+// fused: chunks per workgroup when the caller leaves them to the library
+int64_t fused_fit_chunks(cs_dtype dtype, cs_sampler sampler, int64_t n_chunks);
 size_t fused_workspace_bytes(const StepShape& s);
 void carve_fused_buffers(const Workspace& w, const StepShape& s, FusedBuffers* b);
 int64_t fused_prep_blocks(int64_t n_cells);
