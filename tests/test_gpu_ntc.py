@@ -451,3 +451,61 @@ def test_too_many_candidates(ctx):
     assert st["overflow"] == 1 and st["n_pairs"] == (1 << 31) - 1 and st["n_collided"] == 0
     assert all(np.array_equal(compton.to_host(de)[k], e[k]) for k in "xyzw")
     assert all(np.array_equal(compton.to_host(dg)[k], g[k]) for k in "xyzw")
+
+
+def _cells_plasma(counts_e, counts_g, f, seed, heavy=1.0):
+    """Cells of the given counts with N_e N_g f candidates on average; with
+    heavy > 1 the first electron of each cell carries that weight, so that
+    the other pairs are accepted with 1 / heavy of the probability (chains of
+    many candidates, few collisions)."""
+    rng = np.random.default_rng(seed)
+    counts_e, counts_g = np.asarray(counts_e), np.asarray(counts_g)
+    ne, ng = int(counts_e.sum()), int(counts_g.sum())
+    pm = rng.uniform(0, 2, ne)
+    ux, uy, uz = plasma.isotropic(rng, ne)
+    eps = plasma.log_uniform(rng, ng, 0.05, 2.0)
+    vx, vy, vz = plasma.isotropic(rng, ng)
+    off_e = np.concatenate([[0], np.cumsum(counts_e)]).astype(np.int64)
+    off_g = np.concatenate([[0], np.cumsum(counts_g)]).astype(np.int64)
+    w = np.ones(ne)
+    w[off_e[:-1][counts_e > 0]] = heavy
+    e = {"x": pm * ux, "y": pm * uy, "z": pm * uz, "w": w}
+    g = {"x": eps * vx, "y": eps * vy, "z": eps * vz, "w": np.ones(ng)}
+    return plasma.Plasma("cells", e, g, off_e, off_g, 0.5, f / heavy, seed)
+
+
+@pytest.mark.parametrize("kind", ["limit", "chains", "sparse", "mixed", "dense", "pieces"])
+def test_cells_at_the_limits_of_the_window(ctx, orc, kind):
+    """Cells that fill a window exactly and by one too many, chains as long as
+    both, single cells among thousands of empty ones, cells of 0 .. 200
+    candidates side by side, cells with several windows of candidates left
+    after the parallel rounds, and counts around a piece and a workgroup of
+    the scan.  Tolerance: the module's for FP64 storage."""
+    rng = np.random.default_rng(17)
+    if kind == "limit":
+        p = _cells_plasma([16, 257, 15, 16, 2], [16, 1, 17, 16, 3], 1.0, 21, heavy=16.0)
+        want = [256, 257, 255, 256, 6]
+    elif kind == "chains":
+        p = _cells_plasma([1, 256, 1, 300], [256, 1, 257, 1], 1.0, 22, heavy=32.0)
+        want = [256, 256, 257, 300]
+        p.e["w"][:] = np.where(p.e["w"] > 1, 1.0, p.e["w"])  # unit weights, and one heavy photon in each cell
+        p.g["w"][p.off_g[:-1]] = 32.0
+    elif kind == "sparse":
+        n = np.zeros(5000, dtype=int)
+        n[[0, 1023, 1024, 2500, 4999]] = [4, 5, 6, 1, 3]
+        p, want = _cells_plasma(n, n, 1.0, 23), n * n
+    elif kind == "mixed":
+        p = _cells_plasma(rng.integers(0, 30, 3000), rng.integers(0, 30, 3000), 0.25, 24, heavy=4.0)
+        want = None
+    elif kind == "dense":
+        p, want = _cells_plasma([40] * 30, [40] * 30, 0.5, 25, heavy=16.0), [800] * 30
+    else:
+        n = np.tile([1, 2, 3], 700)[:2049]
+        p, want = _cells_plasma(n, n, 1.0, 26), n * n
+    (st, gst, diag), = _chain_compare(ctx, orc, p, [0])
+    per_cell = np.bincount(diag["cell"], minlength=p.off_e.size - 1)
+    if want is not None:
+        assert np.array_equal(per_cell, want)
+    else:
+        assert per_cell.max() > 150 and (per_cell == 0).any()
+    assert st["n_collided"] > 0
