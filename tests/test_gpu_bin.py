@@ -151,3 +151,20 @@ def test_step_on_gpu_binned_particles(ctx):
         assert np.array_equal(g0[k], g1[k]), k
     assert s0[1] > 0
     assert np.array_equal(s0[:8], s1[:8])
+
+
+@pytest.mark.parametrize("n,n_cells,dtype", [
+    (4096, 300_000, np.float64), (4097, 1, np.float32), (48 * 1024, 40_000, np.float32),
+    (48 * 1024 + 1, 511, np.float64), ((3 << 18) - 1, 512, np.float32), (3 << 18, 32_768, np.float64),
+    ((3 << 20) - 1, 300, np.float32), (3 << 20, 16_384, np.float32), ((3 << 20) + 5, 100_000, np.float32),
+    ((3 << 20) + 5, 200, np.float64)])
+def test_bin_at_the_tile_and_digit_limits(ctx, n, n_cells, dtype):
+    """Particle counts on either side of each tile size (one workgroup, rows of
+    counts, small, medium and large tiles) and cell counts that take one to
+    three digits, even and not, searched by one and by sixteen lanes; some ids
+    invalid."""
+    rng = np.random.default_rng(n + n_cells)
+    cell = rng.integers(0, n_cells, size=n)
+    cell[::1001] = -5
+    cell[7::2003] = n_cells
+    _check(ctx, cell, n_cells, dtype=dtype)
