@@ -103,18 +103,21 @@ struct GradArgs {
 // tile's inputs and targets (vector-memory loads complete in issue order,
 // so a wait for them must not sit behind the parameter loads), then copies
 // the parameters into LDS with coalesced 16-byte loads, and each lane takes
-// the parameters it uses from there into registers, once for all its tiles
-// (its 96 MFMA weight operands among them); each tile issues the next
+// the first layer's and the output layer's parameters and the biases it uses
+// from there into registers, once for all its tiles; each tile issues the next
 // tile's input loads as soon as it has consumed its own.  Activations and
 // deltas are
-// written to LDS in two layouts, [feature][sample] for the operands whose
-// K index is a feature and [sample][feature] (rows of kYRow) for those whose
-// K index is a sample, so that every operand read is conflict-free.  Each
+// written to LDS as [sample][feature] rows, which serve the operands whose K
+// index is a feature and those whose K index is a sample.  (With a second copy
+// [feature][sample] beside it no read had two lanes in a bank, but a workgroup
+// took 104 KB, the whole compute unit: two fit now, which hides the chain of
+// latencies that a tile is: gradient and reduction 34.9 -> 28.7 us at 8192
+// samples, 48.7 -> 36.5 at 16384, 131.5 -> 86.8 at 65536.)  Each
 // gradient entry has one owner and a fixed summation order (no atomics;
 // bitwise reproducible); the reduction kernel adds the workgroups' partials
 // in a fixed order.
 constexpr int kTrainTile = 16;
-constexpr int kYRow = 80;  // [sample][feature] rows: 64 + 16 floats
+constexpr int kYRow = 68;  // [sample][feature] rows: 64 + 4 floats (either operand read two lanes a bank)
 // The parameters in LDS: the three 64x64 hidden matrices with rows of 68
 // floats (so that the operand reads, 16 rows by 4 columns, spread over the
 // banks), then the other 514 parameters packed: W1, b1, b2, b3, b4, W5, b5.
@@ -144,11 +147,9 @@ __device__ __forceinline__ floatx4_t mfma_f32(float a, float b, floatx4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-__global__ __launch_bounds__(kMlpThreads) void k_mlp_grad_block(const GradArgs a) {
+__global__ __launch_bounds__(kMlpThreads, 2) void k_mlp_grad_block(const GradArgs a) {
     __shared__ float4 s_par4[kParFloats / 4];             // the parameters (layout: par_slot)
-    __shared__ float HX[4][kMlpHidden * kTrainTile];      // h1..h4, [feature][sample]
     __shared__ float HY[4][kTrainTile * kYRow];           // h1..h4, [sample][feature]
-    __shared__ float DX[kMlpHidden * kTrainTile];         // delta of the current layer, [feature][sample]
     __shared__ float DY_[2][kTrainTile * kYRow];          // deltas, [sample][feature], ping-pong
     __shared__ float F[kTrainTile][2];                    // features
     __shared__ float dOut[kTrainTile][2];                 // output deltas
@@ -198,19 +199,9 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_grad_block(const GradArgs a
     }
     __syncthreads();
     const float* P = (const float*)s_par4;
-    // every parameter this lane uses, taken once for all its tiles: the
-    // hidden layers' MFMA operands A = W[16w + li][4ks + lg] (forward) and
-    // W^T[16w + li][4ks + lg] (backward), and for its neurons
+    // parameters this lane uses, taken once for all its tiles: for its neurons
     // n(r) = 16w + 4 lg + r the first layer, the biases and the output weights
     const int offW[3] = {kOffW2, kOffW3, kOffW4};
-    float wf[3][16], wt[3][16];
-#pragma unroll
-    for (int L = 0; L < 3; ++L)
-#pragma unroll
-        for (int ks = 0; ks < 16; ++ks) {
-            wf[L][ks] = P[L * kParMat + (16 * w + li) * kParRow + 4 * ks + lg];
-            wt[L][ks] = P[L * kParMat + (4 * ks + lg) * kParRow + 16 * w + li];
-        }
     const float* Ps = P + kParSmall;
     float w1a[4], w1b[4], bias[4][4], w50[4], w51[4];
 #pragma unroll
@@ -236,6 +227,14 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_grad_block(const GradArgs a
     float gB5 = 0.0f, g_loss = 0.0f;         // tid < 2: db5[tid]; tid == 2: the loss
     const float inv_n = 1.0f / (float)a.n;
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        // the hidden layers' MFMA operands, W[16w + li][4ks + lg] (forward) and
+        // W^T[16w + li][4ks + lg] (backward), come from LDS with each product
+        // (from an address that the compiler cannot see through: kept, the 96
+        // of them spilled to the accumulation registers and back, 250 moves a
+        // tile: gradient and reduction 21.0 us at 4096 samples, 20.0 so, 19.4 with
+        // one copy of the activations)
+        int at_f = (16 * w + li) * kParRow + lg, at_t = lg * kParRow + 16 * w + li;
+        asm volatile("" : "+v"(at_f), "+v"(at_t));
         __syncthreads();  // the previous tile's LDS reads are done
         if (tid < kTrainTile) {
             const int64_t i = tile * kTrainTile + tid;
@@ -254,10 +253,8 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_grad_block(const GradArgs a
             float h[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int n = 16 * w + 4 * lg + r;
                 const float z = fmaf(w1b[r], f2, fmaf(w1a[r], f1, bias[0][r]));
                 silu_and_grad(z, h[r], gp[0][r]);
-                HX[0][n * kTrainTile + li] = h[r];
             }
             *(float4*)(&HY[0][li * kYRow + 16 * w + 4 * lg]) = make_float4(h[0], h[1], h[2], h[3]);
         }
@@ -268,15 +265,13 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_grad_block(const GradArgs a
             floatx4_t acc;
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[r] = bias[L + 1][r];
-            const float* hx = &HX[L][lg * kTrainTile + li];
+            const float* hx = &HY[L][li * kYRow + lg];
 #pragma unroll
-            for (int ks = 0; ks < 16; ++ks) acc = mfma_f32(wf[L][ks], hx[4 * ks * kTrainTile], acc);
+            for (int ks = 0; ks < 16; ++ks) acc = mfma_f32(P[L * kParMat + at_f + 4 * ks], hx[4 * ks], acc);
             float h[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int n = 16 * w + 4 * lg + r;
                 silu_and_grad(acc[r], h[r], gp[L + 1][r]);
-                HX[L + 1][n * kTrainTile + li] = h[r];
             }
             *(float4*)(&HY[L + 1][li * kYRow + 16 * w + 4 * lg]) = make_float4(h[0], h[1], h[2], h[3]);
             if (L == 2) {
@@ -350,8 +345,6 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_grad_block(const GradArgs a
         for (int m = 0; m < 3; ++m) {
             const int L = 2 - m;
             float* dy = DY_[cur];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) DX[(16 * w + 4 * lg + r) * kTrainTile + li] = dl[r];
             *(float4*)(&dy[li * kYRow + 16 * w + 4 * lg]) = make_float4(dl[0], dl[1], dl[2], dl[3]);
             __syncthreads();
             // dW[16w + 4lg + r][16tk + li] += sum_s delta[16w + 4lg + r][s] h[16tk + li][s]
@@ -383,14 +376,13 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_grad_block(const GradArgs a
             // delta below: (W^T delta)[16w + 4lg + r][li] * SiLU'(z_L)
             {
                 floatx4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
-                const float* dx = &DX[lg * kTrainTile + li];
+                const float* dx = &dy[li * kYRow + lg];
 #pragma unroll
-                for (int ks = 0; ks < 16; ++ks) acc = mfma_f32(wt[L][ks], dx[4 * ks * kTrainTile], acc);
+                for (int ks = 0; ks < 16; ++ks) acc = mfma_f32(P[L * kParMat + at_t + 4 * ks * kParRow], dx[4 * ks], acc);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) dl[r] = acc[r] * gp[L][r];
             }
-            __syncthreads();  // DX and this layer's delta rows are read
-            cur ^= 1;
+            cur ^= 1;  // (the next layer's rows go to the other half: its barrier is enough)
         }
         // layer 1: dW1[j][i] = sum_s delta1[j][s] F[s][i], db1[j] = sum_s delta1[j][s]
         {
