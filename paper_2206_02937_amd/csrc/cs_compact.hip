@@ -349,8 +349,14 @@ __device__ __forceinline__ int seg_gallop(const int32_t* s, int n, int b0, int32
 // with the plain sampler: the lanes of a wave that need it run it together.
 // (Collecting them for separate dense passes was measured slower: the kernel
 // is bound by the latency of one pass, not by issue.)
+//
+// Three waves per SIMD with a BF16 or FP8 network (by themselves they take 180
+// and 200 registers, two: 2^22 pairs, 209k collisions, BF16 30.5 -> 28.6 us; 2^24
+// pairs, 840k collisions, FP8 136 -> 124 us, near half of it the write-back's
+// partial lines).
 template <typename T, int SAMP>
-__global__ __launch_bounds__(SAMP == CS_SAMPLER_PLAIN ? kDenseThreads : kDenseNetThreads) void k_collide_dense(
+__global__ __launch_bounds__(SAMP == CS_SAMPLER_PLAIN ? kDenseThreads : kDenseNetThreads,
+                             SAMP == CS_SAMPLER_MLP_BF16 || SAMP == CS_SAMPLER_MLP_FP8 ? 3 : 1) void k_collide_dense(
     const CompactArgs<T> a) {
     constexpr int NT = SAMP == CS_SAMPLER_PLAIN ? kDenseThreads : kDenseNetThreads;
     constexpr bool NET = SAMP != CS_SAMPLER_PLAIN;
