@@ -110,8 +110,8 @@ __device__ __forceinline__ void balance_priority(int rem) {
 // list, whose entry q names the stash slot of accepted pair q.
 //
 // Bound by the vector instructions (about 80 % of a compute unit's busy
-// time), 244 per 64 pairs with 256-pair cells and 390 with ragged 64-pair
-// ones; the pairing and the reads are 25 of its 41 us at 2^22 pairs.  At 80
+// time), 224 per 64 pairs with 256-pair cells and 381 with ragged 64-pair
+// ones (292 and 507 before); the pairing and the reads are 25 of its 41 us at 2^22 pairs.  At 80
 // vector registers six waves fit a SIMD (five at 91, with log1p's constants
 // in s(x)).  FP32 storage, plain sampler: 2^22 pairs in 256-pair cells 46.1 ->
 // 41.2 us, in 64-pair cells of uneven filling 85.5 -> 68.7 us, 2^24 pairs

@@ -363,8 +363,9 @@ __device__ __forceinline__ bool weight_ok(double w) { return __builtin_isfpclass
 //
 // Every lane evaluates every step, and what an inactive or invalid lane gets
 // is replaced at the end: kept in branches of their own, the steps cost the
-// initial values and selects of everything they define (292 vector
-// instructions per 64 pairs for the whole pair kernel, 244 now).  (1 + p.p) k.k in
+// initial values and selects of everything they define (with it the
+// pair kernel takes 224 vector instructions per 64 pairs in 256-pair cells, 292
+// before).  (1 + p.p) k.k in
 // [1e-300, 1e300] implies finite momenta, so one range test per lane stands
 // for the six finiteness tests and for x_flux's own; a wave with an active
 // lane outside it (or with an unusable weight) takes the general form, whose
