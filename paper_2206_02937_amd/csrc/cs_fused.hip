@@ -213,8 +213,8 @@ __device__ __forceinline__ void step_fetch(const FusedArgs<T>& a, int32_t t_wave
 // vector instructions of the pairs and of the sampler.  FP32 storage, plain
 // sampler, against one queue per workgroup, three barriers per chunk and
 // nothing read ahead: 2^22 pairs in 256-pair cells 119.8 -> 63.4 us, in
-// 64-pair cells of uneven filling 168 -> 95 us, 2^20 pairs 41.1 -> 25.7 us,
-// 2^24 pairs 416 -> 258 us; FP64 storage 142.9 -> 83.2 us at 2^22 pairs; BF16
+// 64-pair cells of uneven filling 168 -> 93 us, 2^20 pairs 41.1 -> 24.9 us,
+// 2^24 pairs 416 -> 258 us; FP64 storage 142.9 -> 81.6 us at 2^22 pairs; BF16
 // network 139 -> 98 us.  With the plain sampler on FP32 storage four waves
 // per SIMD are asked for (126 registers; the 143 it takes by itself allow
 // three: 76 us where four take 62; five, with spills, 75).
@@ -242,7 +242,20 @@ __global__ __launch_bounds__(kChunk, SAMP == CS_SAMPLER_PLAIN && sizeof(T) == 4 
     const int tid = threadIdx.x;
     const int lane = lane_id();
     const int wave = wave_uniform(tid >> 6);
-    for (int i = tid; i < kSigTabSegments * kSigTabTerms; i += kChunk) s_sig[i] = kSigTab[i];
+    // The s(x) table, the control words, the pair count and the first chunk's
+    // cells are read together, and the table stored to LDS behind them: one
+    // after another they are three memory round trips at the start of every
+    // workgroup (this kernel at 2^20 pairs: FP32 25.6 -> 24.9 us, FP64 28.3 ->
+    // 27.5 us; at 2^22 FP64 82.5 -> 81.6 us; the rest unchanged).
+    constexpr int kSigRounds = kSigTabSegments * kSigTabTerms / kChunk;
+    static_assert(kSigRounds * kChunk == kSigTabSegments * kSigTabTerms, "whole rounds");
+    double sig_v[kSigRounds];
+#pragma unroll
+    for (int r = 0; r < kSigRounds; ++r) sig_v[r] = kSigTab[tid + r * kChunk];
+    const int64_t j_begin = (int64_t)blockIdx.x * a.chunks_per_block;
+    const int64_t j_read = j_begin < a.n_chunks ? j_begin : a.n_chunks;  // (n_chunks + 1 entries)
+    const int c_first = ld_uniform(a.chunk_cell, j_read);
+    int c_next = ld_uniform(a.chunk_cell, j_read < a.n_chunks ? j_read + 1 : j_read);
     StepControl* ctrl = a.ctrl;
     const int32_t T_read = a.pair_off[a.n_cells];
     const CtrlView cv = ctrl_view(ctrl);
@@ -251,10 +264,11 @@ __global__ __launch_bounds__(kChunk, SAMP == CS_SAMPLER_PLAIN && sizeof(T) == 4 
     long long n_clip = 0, n_inv = 0, n_coll = 0;  // wave-uniform
     CollideSums sums;
     net_load<SAMP>(s_net, a.mlp);
+#pragma unroll
+    for (int r = 0; r < kSigRounds; ++r) s_sig[tid + r * kChunk] = sig_v[r];
     // (no pair at all under a layout error; reads past the map then too)
     const int32_t T_total = cv.layout_ok ? T_read : 0;
     const int64_t n_used = ((int64_t)T_total + kChunk - 1) / kChunk;
-    const int64_t j_begin = (int64_t)blockIdx.x * a.chunks_per_block;
     int64_t j_end = j_begin + a.chunks_per_block;
     if (j_end > a.n_chunks) j_end = a.n_chunks;
     if (j_end > n_used) j_end = n_used;
@@ -266,12 +280,8 @@ __global__ __launch_bounds__(kChunk, SAMP == CS_SAMPLER_PLAIN && sizeof(T) == 4 
     __syncthreads();
     PairSlot sl = {0, 0, 0, false};
     PairRaw<T> raw = {};
-    int c_next = 0;
-    if (j_begin < j_end) {
-        c_next = ld_uniform(a.chunk_cell, j_begin + 1);
-        step_fetch<T, O32>(a, (int32_t)(j_begin * kChunk) + 64 * wave, T_total, ld_uniform(a.chunk_cell, j_begin),
-                           c_next, sl, raw);
-    }
+    if (j_begin < j_end)
+        step_fetch<T, O32>(a, (int32_t)(j_begin * kChunk) + 64 * wave, T_total, c_first, c_next, sl, raw);
     for (int64_t j = j_begin;; ++j) {
         const FusedArgs<T>& a = *own();
         const bool last = j >= j_end;  // uniform over the block
