@@ -395,7 +395,7 @@ __global__ __launch_bounds__(SAMP == CS_SAMPLER_PLAIN ? kDenseThreads : kDenseNe
     // (whole tiles) when that many still cover the list in one pass, because
     // the wave's time then is that of the tiles it evaluates one after another
     // (beam-gas plasma of 2^20 pairs, 16 k collisions, FP32 network: the kernel
-    // takes 33.9 us at 64 per wave, 24.5 us at 16)
+    // takes 34 us at 64 per wave, 25 us at 16)
     const int64_t n_waves = (int64_t)gridDim.x * (NT / 64);
     const int per_wave = !NET || A > 32 * n_waves ? 64 : (A > 16 * n_waves ? 32 : 16);
     const int64_t stride = n_waves * per_wave;

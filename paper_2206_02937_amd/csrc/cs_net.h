@@ -35,10 +35,14 @@ constexpr float kE4M3Max = 448.0f;
 
 __device__ __forceinline__ float silu_f32(float z) { return z / (1.0f + expf(-z)); }
 
-// The same for FP32 inference, in half the instructions: e^-z from the
-// hardware exp2 with the rounding of its argument compensated (within 1.5
+// The same for FP32 inference, in two thirds of the instructions: e^-z from
+// the hardware exp2 with the rounding of its argument compensated (within 1.5
 // ulp), and the quotient from the reciprocal estimate and one residual
-// correction (correctly rounded but for near-ties).  -z is capped at 87,
+// correction, which also takes in what the sum 1 + e^-z lost to rounding.
+// Error of the network's outputs against 64 bits, rms over 12 sets of 2^20
+// inputs: 9.28e-8 and 7.42e-8 (without the sum's rounding 9.40e-8 and
+// 7.52e-8, at 1218 us for 2^22 samples in place of 1314 us; with silu_f32
+// 9.38e-8 and 7.53e-8).  -z is capped at 87,
 // where SiLU is below 1e-36, so that the denominator stays finite (a NaN
 // passes through the quotient).
 __device__ __forceinline__ float silu_f32_fast(float z) {
@@ -47,10 +51,12 @@ __device__ __forceinline__ float silu_f32_fast(float z) {
     // y log2(e) - t: the product's rounding and log2(e)'s
     const float d = fmaf(y, 1.92596299e-8f, fmaf(y, 1.44269504f, -t));
     const float ex = __builtin_amdgcn_exp2f(t);
-    const float den = 1.0f + fmaf(ex, 0.69314718f * d, ex);
+    const float em = fmaf(ex, 0.69314718f * d, ex);
+    const float den = 1.0f + em;
+    const float lost = em - (den - 1.0f);  // exact up to den = 2^24
     const float r = __builtin_amdgcn_rcpf(den);
     const float q = z * r;
-    return fmaf(fmaf(-den, q, z), r, q);
+    return fmaf(fmaf(-lost, q, fmaf(-den, q, z)), r, q);
 }
 
 // The reduced-precision paths carry every pre-activation and activation of
@@ -303,9 +309,9 @@ __device__ __forceinline__ void mlp_tile(const typename FragT<PREC>::type* frag,
 // the vector ALUs.  What bounds it: the FP32 matrix rate (768 products of 32
 // cycles per 64 samples) and SiLU on the vector ALUs (256 per sample), which
 // overlap little: 2^22 samples 1552 us with single-float fragment reads and
-// the IEEE quotient, 1216 us with this.  In the collide kernel it replaced one
+// the IEEE quotient, 1314 us with this.  In the collide kernel it replaced one
 // sample per lane on the vector ALUs (65 KB of LDS for the activations):
-// 107 us -> 33.9 us on the beam-gas plasma of 2^20 pairs (16 k collisions).
+// 107 us -> 34 us on the beam-gas plasma of 2^20 pairs (16 k collisions).
 constexpr int kF32Frag = 3 * 4 * 4 * 64;  // 16-byte entries [layer][T][t][lane], 48 KB
 
 // Parameter index of the first of entry i's four weights.
