@@ -135,21 +135,21 @@ __device__ __forceinline__ void outer_acc(floatx4_p& acc, float* sd, float* sa, 
         A[j] = *(const float4*)(pa + 4 * j);
         if (c == NI) A[j] = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
     }
-    // four chains, added in pairs: what one chain over the 64 pairs loses to
-    // rounding is more than a tree of sums does (the gradient's error against 64
-    // bits, 1000 pairs, relative rms: 9.0e-8 with one, 7.7e-8 with four, 7.4e-8
-    // with butterfly sums over the lanes; 65536 pairs: 6.3e-8, 6.0e-8, 2.3e-7)
-    floatx4_p s[4];
+    // two chains over half the pairs each: 2^22 pairs 188 us, with four chains
+    // 200 us; the gradient's relative error against 64 bits at 1024 pairs is
+    // 2.8e-8 with two, 2.6e-8 with four
+    floatx4_p s[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) s[j] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        s[j] = {0.0f, 0.0f, 0.0f, 0.0f};
-        s[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(D[j].x, A[j].x, s[j], 0, 0, 0);
-        s[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(D[j].y, A[j].y, s[j], 0, 0, 0);
-        s[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(D[j].z, A[j].z, s[j], 0, 0, 0);
-        s[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(D[j].w, A[j].w, s[j], 0, 0, 0);
+        s[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(D[j].x, A[j].x, s[j & 1], 0, 0, 0);
+        s[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(D[j].y, A[j].y, s[j & 1], 0, 0, 0);
+        s[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(D[j].z, A[j].z, s[j & 1], 0, 0, 0);
+        s[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(D[j].w, A[j].w, s[j & 1], 0, 0, 0);
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) acc[r] += (s[0][r] + s[1][r]) + (s[2][r] + s[3][r]);
+    for (int r = 0; r < 4; ++r) acc[r] += s[0][r] + s[1][r];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
@@ -181,10 +181,10 @@ __device__ __forceinline__ float relu_delta(float a, float v) {
 // layers: with the reduction 79.5 us per call with a butterfly sum over the
 // wave per parameter (and one thread per parameter walking the partials),
 // 11.5 us with this, most of it the two launches; at 2^22 pairs VALU issue
-// and the matrix cores, 6509 and 203 us.
+// and the matrix cores, 6509 and 188 us.
 __global__ __launch_bounds__(kPnetThreads) void k_pnet_grad_block(const float* params, const float* in,
                                                                 const float* target, int64_t n, int mae,
-                                                                float* partials) {
+                                                                double* partials) {
     __shared__ __align__(16) float s_buf[kPnetThreads / 64][2 * kPnetRows * kPnetRow];
     __shared__ float s_part[kPnetThreads / 64][kPnetPart];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -258,28 +258,33 @@ __global__ __launch_bounds__(kPnetThreads) void k_pnet_grad_block(const float* p
     }
     __syncthreads();
     for (int q = tid; q < kPnetPart; q += kPnetThreads) {
-        float t = 0.0f;
+        double t = 0.0;
 #pragma unroll
-        for (int w = 0; w < kPnetThreads / 64; ++w) t += s_part[w][q];
+        for (int w = 0; w < kPnetThreads / 64; ++w) t += (double)s_part[w][q];
         partials[(int64_t)blockIdx.x * kPnetPart + q] = t;
     }
 }
 
 // One workgroup of 16 waves per 64 entries: wave w sums the partials of the
 // workgroups b = 16 c + w (c ascending, eight reads in flight), then wave 0
-// adds the 16 wave sums in order.
+// adds the 16 wave sums in order.  The sums over waves and workgroups are in
+// FP64, rounded once at the end: the gradient's relative error against 64 bits
+// (mean of ten sets) at 4096, 40000 and 10^6 pairs is 2.5e-8, 2.5e-8 and
+// 2.6e-7; with FP32 sums 6.1e-8, 6.3e-8 and 2.9e-7, at the same time per call;
+// with butterfly sums over the lanes and one FP32 chain over the workgroups
+// 6.3e-8, 1.9e-7 and 9.6e-7.
 constexpr int kPnetReduceWaves = 16;
 
-__global__ __launch_bounds__(64 * kPnetReduceWaves) void k_pnet_reduce(const float* partials, int64_t n_blocks,
+__global__ __launch_bounds__(64 * kPnetReduceWaves) void k_pnet_reduce(const double* partials, int64_t n_blocks,
                                                                       int64_t n, float* grad, float* loss) {
-    __shared__ float s_q[kPnetReduceWaves][64];
+    __shared__ double s_q[kPnetReduceWaves][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int q = blockIdx.x * 64 + lane;
     const int qc = q < kPnetPart ? q : kPnetPart - 1;
-    float t = 0.0f;
+    double t = 0.0;
     int64_t b = w;
     for (; b + 7 * kPnetReduceWaves < n_blocks; b += 8 * kPnetReduceWaves) {
-        float v[8];
+        double v[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) v[k] = partials[(b + kPnetReduceWaves * k) * kPnetPart + qc];
 #pragma unroll
@@ -292,7 +297,7 @@ __global__ __launch_bounds__(64 * kPnetReduceWaves) void k_pnet_reduce(const flo
     t = s_q[0][lane];
 #pragma unroll
     for (int k = 1; k < kPnetReduceWaves; ++k) t += s_q[k][lane];
-    const float v = n > 0 ? t / (float)n : 0.0f;
+    const float v = n > 0 ? (float)(t / (double)n) : 0.0f;
     if (q < kPnetParams)
         grad[q] = v;
     else if (loss)
@@ -322,7 +327,7 @@ static int64_t pnet_grad_blocks(int64_t n) {
 
 size_t pnet_workspace_bytes(int64_t n) {
     const int64_t nb = n > 0 ? pnet_grad_blocks(n) : 1;
-    return sizeof(float) * (size_t)nb * kPnetPart;
+    return sizeof(double) * (size_t)nb * kPnetPart;
 }
 
 hipError_t launch_pnet_target(const float* in, int64_t n, float* y, hipStream_t st) {
@@ -339,7 +344,7 @@ hipError_t launch_pnet_forward(const float* params, const float* in, int64_t n, 
 hipError_t launch_pnet_grad(const float* params, const float* in, const float* target, int64_t n, int mae,
                             float* grad, float* loss, void* ws, hipStream_t st) {
     const int64_t nb = n > 0 ? pnet_grad_blocks(n) : 0;
-    float* part = (float*)ws;
+    double* part = (double*)ws;
     if (nb > 0) k_pnet_grad_block<<<(unsigned)nb, kPnetThreads, 0, st>>>(params, in, target, n, mae, part);
     k_pnet_reduce<<<(kPnetPart + 63) / 64, 64 * kPnetReduceWaves, 0, st>>>(part, nb, n, grad, loss);
     return hipGetLastError();
