@@ -301,13 +301,29 @@ __device__ __forceinline__ double sigma_ratio_tab(double x, const double* tab) {
 
 __device__ __forceinline__ double sigma_ratio(double x) { return sigma_ratio_tab(x, kSigTab); }
 
-// (8/3) s(x) = T(2): the whole angular integral.
+// (8/3) s(x) = T(2): the whole angular integral.  Below kMidX as polynomials in
+// x, whose rounding takes 0.7e-16 of it (rms), where the tail itself loses 1.7e-16 (with
+// which the sampled v was 2.5e-16 off, for x in [2^-8, 0.1); 1.9e-16 so).  Above, the
+// tail's rounding errors at 2 and at v are partly the same.
 __device__ __forceinline__ double kn_total(double x) {
     if (x < kSmallX) {
         double z = kSmallZ[kSmallZTerms - 1];
 #pragma unroll
         for (int k = kSmallZTerms - 2; k >= 0; --k) z = fma_sgpr(z, x, kSmallZ[k]);
         return z;
+    }
+    if (x < kMidX) {
+        cdptr c = (cdptr)kMidZ;
+        asm volatile("" : "+s"(c));
+        static_assert(kMidZTerms % 2 == 0, "two chains of equal length");
+        const double t = x - kMidC, t2 = t * t;
+        double e = c[kMidZTerms - 2], o = c[kMidZTerms - 1];
+#pragma unroll
+        for (int k = kMidZTerms - 4; k >= 0; k -= 2) {
+            e = fma_sgpr(e, t2, c[k]);
+            o = fma_sgpr(o, t2, c[k + 1]);
+        }
+        return fma(o, t, e);
     }
     return kn_tail(2.0, x).T;
 }

@@ -38,6 +38,26 @@ __constant__ constexpr double kSmallZ[8] = {
     -1.09297777777777787e+03,
 };
 
+// the same in powers of x - kMidC, for kSmallX <= x < kMidX
+constexpr double kMidX = 0.125, kMidC = 0.06666851043701172;
+constexpr int kMidZTerms = 14;
+__constant__ constexpr double kMidZ[14] = {
+    2.36371039173310171e+00,
+    -3.87124334961286065e+00,
+    8.60070829245241519e+00,
+    -1.91943691639883376e+01,
+    4.14460160206864074e+01,
+    -8.67955543987861660e+01,
+    1.77426473765123063e+02,
+    -3.55955114485484614e+02,
+    7.03684685697307941e+02,
+    -1.37485154058525904e+03,
+    2.65804434265405007e+03,
+    -5.08969110728220221e+03,
+    1.01846937630780321e+04,
+    -2.05014720342007313e+04,
+};
+
 // h(w, t), t = L / (L + kStartShift): relative error of v 1.0e-02
 constexpr float kStartShift = 2.0f;
 constexpr int kStartRows = 5;

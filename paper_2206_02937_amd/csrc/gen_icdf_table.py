@@ -11,13 +11,17 @@ kTailPoly   P(sigma) = sum_k 2 sigma^k / (2k + 3) on [0, 1/4], degree 15: the
             1.5e-17 relative (beyond the rounding of its leading term).
 kSmallZ     (8/3) s(x) about x = 0 to x^7, for x < 2^-8 (the next term is
             below 2e-17 there).
+kMidZ       the same for 2^-8 <= x < 1/8, in powers of x - kMidC: the Chebyshev
+            interpolant (its nearest singularity, x = -1/2, is 9.3 half-widths
+            from the centre, so the error falls by 18.6 per degree); kMidC, near
+            the middle, is where the leading coefficient is a double to 1e-18.
 kStart*     FP32 starting values of the root, fitted to the exact inverse by
             reweighted least squares (about minimax in the relative error of
             v): with w = 1 - u, L = ln(1 + 2x), t = L / (L + 2),
               h(w, t) = ln(1 + x v) / (L w) = sum_j t^j row_j(w)
             over 0 <= x <= 1000 (relative error of v 1e-2), and
               v / w = A(w) + x B(w)
-            over 0 <= x < 2^-8 (6e-4), and P once more to FP32 accuracy.  They
+            over 0 <= x < 2^-8 (8e-4), and P once more to FP32 accuracy.  They
             have to be good enough for one FP32 step (of third order, and of
             second for the small x) to reach about 1e-6.
 """
@@ -31,6 +35,7 @@ OUT = os.path.join(HERE, "cs_icdf_table.h")
 TAIL_TERMS = 16
 SMALL_Z_TERMS = 8
 SMALL_X = 2.0 ** -8
+MID_X, MID_C, MID_Z_TERMS = 0.125, 0.06666851043701172, 14
 X_MAX = 1000.0
 T_SHIFT = 2.0
 ROWS = (5, 5, 5, 4, 3)  # degree in w of row j
@@ -64,12 +69,30 @@ def tail_poly():
     return dbl
 
 
-def small_z():
-    def s_closed(x):
-        l = mp.log1p(2 * x)
-        return mp.mpf(2) * ((1 + x) / x ** 3 * (2 * x * (1 + x) / (1 + 2 * x) - l) + l / (2 * x)
-                            - (1 + 3 * x) / (1 + 2 * x) ** 2)
+def total(x):
+    """(8/3) s(x), closed form (use at 60 digits)."""
+    l = mp.log1p(2 * x)
+    return mp.mpf(2) * ((1 + x) / x ** 3 * (2 * x * (1 + x) / (1 + 2 * x) - l) + l / (2 * x)
+                        - (1 + 3 * x) / (1 + 2 * x) ** 2)
 
+
+def mid_z():
+    n, lo, hi, c = MID_Z_TERMS, mp.mpf(SMALL_X), mp.mpf(MID_X), mp.mpf(MID_C)
+    nodes = [(lo + hi) / 2 + (hi - lo) / 2 * mp.cos(mp.pi * (2 * i + 1) / (2 * n)) for i in range(n)]
+    a, b = mp.matrix(n, n), mp.matrix(n, 1)
+    for i, x in enumerate(nodes):
+        b[i] = total(x)
+        for k in range(n):
+            a[i, k] = (x - c) ** k
+    out = [float(v) for v in mp.lu_solve(a, b)]
+    for i in range(300):
+        x = lo + (hi - lo) * i / 299
+        got = sum(mp.mpf(v) * (x - c) ** k for k, v in enumerate(out))
+        assert abs(got / total(x) - 1) < mp.mpf("4e-17"), (float(x), float(got / total(x) - 1))
+    return out
+
+
+def small_z():
     # (8/3) s(x) = int_0^2 f dv with f expanded in x: a^-m = sum binom(-m, k) (x v)^k
     out = []
     for k in range(SMALL_Z_TERMS):
@@ -78,7 +101,7 @@ def small_z():
         out.append((c3 + c1) * v ** (k + 1) / (k + 1) - c2 * (2 * v ** (k + 2) / (k + 2) - v ** (k + 3) / (k + 3)))
     x = mp.mpf(SMALL_X)
     got = sum(c * x ** k for k, c in enumerate(out))
-    assert abs(got / s_closed(x) - 1) < mp.mpf("1e-16"), float(got / s_closed(x) - 1)
+    assert abs(got / total(x) - 1) < mp.mpf("1e-16"), float(got / total(x) - 1)
     return [float(c) for c in out]
 
 
@@ -159,7 +182,7 @@ def start_tail():
 
 def main():
     mp.mp.dps = 60
-    tail, sz = tail_poly(), small_z()
+    tail, sz, mz = tail_poly(), small_z(), mid_z()
     e_rows, rows = start_rows()
     e_small, a, b = start_small()
     e_tail, pt = start_tail()
@@ -182,6 +205,13 @@ def main():
         f"constexpr int kSmallZTerms = {SMALL_Z_TERMS};",
         f"__constant__ constexpr double kSmallZ[{SMALL_Z_TERMS}] = {{",
         *["    %.17e," % v for v in sz],
+        "};",
+        "",
+        "// the same in powers of x - kMidC, for kSmallX <= x < kMidX",
+        f"constexpr double kMidX = {MID_X!r}, kMidC = {MID_C!r};",
+        f"constexpr int kMidZTerms = {MID_Z_TERMS};",
+        f"__constant__ constexpr double kMidZ[{MID_Z_TERMS}] = {{",
+        *["    %.17e," % v for v in mz],
         "};",
         "",
         f"// h(w, t), t = L / (L + kStartShift): relative error of v {e_rows:.1e}",
