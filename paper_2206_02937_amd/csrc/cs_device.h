@@ -215,12 +215,18 @@ __device__ __forceinline__ double tail_poly(double sg) {
 // series: for z < 2 of s = z / (2 + z), above of (m - 1) / (m + 1) with
 // A = 2^k m, m in [1/sqrt 2, sqrt 2), whose logarithm takes the same P.
 // ANY_BIG = false: for waves without a lane of z >= 2 (the same arithmetic
-// for the others).
+// for the others).  ROUND: where z >= 2, every operation rounded (what the
+// shipped network's training targets, x up to 1e3, were made with), or two
+// roundings fewer, or these above kTailFusedX, where the root takes up more of
+// them.
 struct KnTail {
     double T, iA, w;
 };
 
-template <bool ANY_BIG>
+enum TailRound { kTailPlain, kTailFused, kTailByX };
+constexpr double kTailFusedX = 1e3;
+
+template <bool ANY_BIG, TailRound ROUND>
 __device__ __forceinline__ KnTail kn_tail_z(double v, double x, double z, bool big) {
     const double t2 = z + 2.0, A = z + 1.0;
     double num = z, den = t2, k = 0.0;
@@ -254,16 +260,19 @@ __device__ __forceinline__ KnTail kn_tail_z(double v, double x, double z, bool b
         const double lnA = fma(k, 0x1.62e42feep-1, fma(k, 0x1.a39ef35793c76p-33, l));
         const double ix = recip_approx(x), zA = z * o.iA;
         const double phi2 = lnA - zA, phi3 = (z - 2.0 * lnA) + zA;
-        o.T = first + ix * (lnA - ix * (2.0 * phi2 - phi3 * ix));
+        const double y = 2.0 * phi2 - phi3 * ix;
+        const double plain = first + ix * (lnA - ix * y), fused = fma(ix, fma(-ix, y, lnA), first);
+        o.T = ROUND == kTailPlain ? plain : (ROUND == kTailFused || x > kTailFusedX ? fused : plain);
     }
     return o;
 }
 
+template <TailRound ROUND = kTailPlain>
 __device__ __forceinline__ KnTail kn_tail(double v, double x) {
     const double z = x * v;
     const bool big = z >= 2.0;
-    if (any_lane(big)) return kn_tail_z<true>(v, x, z, big);
-    return kn_tail_z<false>(v, x, z, false);
+    if (any_lane(big)) return kn_tail_z<true, ROUND>(v, x, z, big);
+    return kn_tail_z<false, ROUND>(v, x, z, false);
 }
 
 // s(x) = sigma_KN(x) / sigma_T.  Below 2: the per-segment Taylor polynomial
@@ -406,8 +415,9 @@ struct IcdfStep {
     double R, d, c2;  // residual, Newton step, d f' / (2 f)
 };
 
+template <TailRound ROUND = kTailPlain>
 __device__ __forceinline__ IcdfStep icdf_step(double v, double x, double target) {
-    const KnTail t = kn_tail(v, x);
+    const KnTail t = kn_tail<ROUND>(v, x);
     const double a2 = t.iA * t.iA;
     const double h = fma(-t.iA, t.w, 1.0 + a2);
     const double f = t.iA * h;
@@ -422,12 +432,14 @@ __device__ __forceinline__ IcdfStep icdf_step(double v, double x, double target)
     return s;
 }
 
-// More steps where one did not settle it (a start far off: x beyond the
-// fitted range), safeguarded by a bisection bracket.
-__device__ __attribute__((noinline)) double icdf_refine(double v, double x, double target) {
+// More steps where one did not settle it, safeguarded by a bisection bracket
+// (a start far off), and every x above kTailFusedX, target and residual with
+// the fewer roundings (x in [1e3, 1e4): v 7.7e-16 -> 6.9e-16 off, rms).
+__device__ __attribute__((noinline)) double icdf_refine(double v, double x, double w1, double target) {
     double lo = 0.0, hi = 2.0;
+    if (x > kTailFusedX) target = w1 * kn_tail<kTailFused>(2.0, x).T;
     for (int it = 0; it < 60; ++it) {
-        const IcdfStep s = icdf_step(v, x, target);
+        const IcdfStep s = icdf_step<kTailByX>(v, x, target);
         double next = v - fma(s.d, fabs(s.c2) < 0.5 ? s.c2 : 0.0, s.d);
         if (fabs(s.d) <= 3e-6 * v) return next;
         if (s.R > 0.0)  // v too large
@@ -468,9 +480,9 @@ __device__ __forceinline__ double angle_icdf_v(double u, double x) {
     const double v = (double)__builtin_amdgcn_fmed3f(start, 0.0f, 2.0f);
     const IcdfStep s = icdf_step(v, x, target);
     double next = v - fma(s.d, s.c2, s.d);
-    const bool settled = fabs(s.d) <= 3e-6 * v;
-    if (any_lane(!settled)) {
-        if (!settled) next = icdf_refine(v, x, target);
+    const bool settled = fabs(s.d) <= 3e-6 * v && x <= kTailFusedX;
+    if (__builtin_expect(any_lane(!settled), 0)) {
+        if (!settled) next = icdf_refine(v, x, w1, target);
     }
     return fmin(next, 2.0);
 }

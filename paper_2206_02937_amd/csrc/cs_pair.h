@@ -663,7 +663,7 @@ __device__ __forceinline__ void collide_net(const Particles<T>& a, bool active, 
     if (inside) features(xf, uf, m.dom, f1, f2);
     const float2 y = net_outputs<SAMP>(s_net, m, inside, f1, f2);
     double v = 0.0;
-    if (__any(fallback)) {
+    if (__builtin_expect(__any(fallback), 0)) {
         const double vf = angle_icdf_v(fallback ? u : 0.5, fallback ? x : 0.0);
         if (fallback) v = vf;
     }

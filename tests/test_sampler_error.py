@@ -128,6 +128,7 @@ def model(tmp_path_factory):
 @pytest.mark.parametrize("x0, x1, bound", [
     (1e-8, 1e-3, 2.30e-16), (1e-3, 2.0 ** -8, 2.30e-16), (2.0 ** -8, 0.03, 2.32e-16), (0.03, 0.1, 2.41e-16),
     (0.1, 0.15, 2.80e-16), (0.15, 0.5, 2.81e-16), (0.5, 1.0, 3.10e-16), (1.0, 10.0, 3.80e-16),
-    (10.0, 100.0, 4.41e-16), (100.0, 1e3, 6.01e-16)])
+    (10.0, 100.0, 4.41e-16), (100.0, 1e3, 6.01e-16), (1e3, 1e4, 7.60e-16), (1e4, 2.0 ** 17, 9.80e-16),
+    (2.0 ** 17, 1e9, 1.75e-15)])
 def test_root_error(model, x0, x1, bound):
     assert model(x0, x1)[0] <= bound
