@@ -305,7 +305,7 @@ __device__ __forceinline__ double sigma_ratio_tab(double x, const double* tab) {
         for (int n = kSigTabTerms - 2; n >= 0; --n) acc = fma(acc, t, a[n]);
         return acc;
     }
-    return 0.375 * kn_tail(2.0, x).T;
+    return 0.375 * kn_tail<kTailFused>(2.0, x).T;
 }
 
 __device__ __forceinline__ double sigma_ratio(double x) { return sigma_ratio_tab(x, kSigTab); }

@@ -132,3 +132,9 @@ def model(tmp_path_factory):
     (2.0 ** 17, 1e9, 1.75e-15)])
 def test_root_error(model, x0, x1, bound):
     assert model(x0, x1)[0] <= bound
+
+
+@pytest.mark.parametrize("x0, x1, bound", [(2.0 ** -20, 2.0 ** 17, 7.0e-17), (2.0 ** 17, 1e6, 1.09e-16),
+                                           (1e6, 1e9, 1.12e-16), (1e9, 1e15, 1.07e-16)])
+def test_cross_section_error(model, x0, x1, bound):
+    assert model(x0, x1)[1] <= bound
