@@ -6,7 +6,8 @@
 //     kernels build the fragments (BF16 rounding, or per-layer FP8 scales
 //     from the weight amax and a calibration pass of the FP32 engine);
 //   * FP32 inference and calibration: the same walk with FP32 MFMA
-//     (v_mfma_f32_16x16x4_f32) and the correctly rounded FP32 SiLU;
+//     (v_mfma_f32_16x16x4_f32), calibration with the correctly rounded FP32
+//     SiLU, inference with silu_f32_fast;
 //   * training: forward and backward of 16-sample tiles on FP32 MFMA, one
 //     partial gradient per workgroup, then a fixed-order sum of the partials
 //     and Adam (bitwise reproducible).
@@ -692,13 +693,14 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_mlp_f32(const FwdArgs a) {
         const float x = active ? a.x[i] : 1.0f, u = active ? a.u[i] : 0.5f;
         float f1, f2;
         features(x, u, a.dom, f1, f2);
-        int opaque = 0;
-        asm volatile("" : "+s"(opaque));
-        const float4* frag = s_net.frag + opaque;
-        const float* Ps = s_net.P + opaque;
         float o0 = 0.0f, o1 = 0.0f;
 #pragma unroll
         for (int t0 = 0; t0 < 4; t0 += 2) {
+            // (the weights read again for each pair of tiles, not kept)
+            int opaque = 0;
+            asm volatile("" : "+s"(opaque));
+            const float4* frag = s_net.frag + opaque;
+            const float* Ps = s_net.P + opaque;
             float g1[2], g2[2], y0[2], y1[2];
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
@@ -710,7 +712,7 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_mlp_f32(const FwdArgs a) {
             // of tile t0 + k evaluates sample 16 (t0 + k) + li of the group
             const bool real[2] = {grp * 64 + 16 * t0 + (lane & 15) < a.n,
                                   grp * 64 + 16 * (t0 + 1) + (lane & 15) < a.n};
-            mlp_tiles_f32<2, CALIB>(frag, Ps, g1, g2, y0, y1, CALIB ? amax : nullptr, real);
+            mlp_tiles_f32<2, CALIB ? kSiluExact : kSiluFast>(frag, Ps, g1, g2, y0, y1, CALIB ? amax : nullptr, real);
 #pragma unroll
             for (int k = 0; k < 2; ++k)
                 if ((lane >> 4) == t0 + k) {
@@ -718,6 +720,7 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_mlp_f32(const FwdArgs a) {
                     o1 = y1[k];
                 }
         }
+        if (!CALIB) mlp_redo_f32(s_net.frag, s_net.P, f1, f2, o0, o1);
         if (active && a.y) *(float2*)(a.y + 2 * i) = make_float2(o0, o1);
         if (sampling && active && in_range(x, a.dom)) net_out(a, i, x, o0, o1);
     }

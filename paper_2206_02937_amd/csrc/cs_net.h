@@ -41,15 +41,13 @@ __device__ __forceinline__ float silu_f32(float z) { return z / (1.0f + expf(-z)
 // correction, which also takes in what the sum 1 + e^-z lost to rounding.
 // Error of the network's outputs against 64 bits, rms over 12 sets of 2^20
 // inputs: 9.28e-8 and 7.42e-8 (without the sum's rounding 9.40e-8 and
-// 7.52e-8, at 1218 us for 2^22 samples in place of 1314 us; with silu_f32
-// 9.38e-8 and 7.53e-8).  -z is capped at 87,
-// where SiLU is below 1e-36, so that the denominator stays finite (a NaN
-// passes through the quotient).
+// 7.52e-8; with silu_f32 9.38e-8 and 7.53e-8).  A NaN for z below -88.7, where
+// e^-z leaves the range, and for +inf (and for NaN); -0 from -87.4 down to there,
+// z from 17 up.
 __device__ __forceinline__ float silu_f32_fast(float z) {
-    const float y = __builtin_amdgcn_fmed3f(-z, -126.0f, 87.0f);
-    const float t = y * 1.44269504f;
-    // y log2(e) - t: the product's rounding and log2(e)'s
-    const float d = fmaf(y, 1.92596299e-8f, fmaf(y, 1.44269504f, -t));
+    const float t = z * -1.44269504f;
+    // -z log2(e) - t: the product's rounding and log2(e)'s
+    const float d = fmaf(z, -1.92596299e-8f, fmaf(z, -1.44269504f, -t));
     const float ex = __builtin_amdgcn_exp2f(t);
     const float em = fmaf(ex, 0.69314718f * d, ex);
     const float den = 1.0f + em;
@@ -57,6 +55,11 @@ __device__ __forceinline__ float silu_f32_fast(float z) {
     const float r = __builtin_amdgcn_rcpf(den);
     const float q = z * r;
     return fmaf(fmaf(-lost, q, fmaf(-den, q, z)), r, q);
+}
+
+// The same, and 0 or z where that is a NaN (but for z = NaN).
+__device__ __forceinline__ float silu_f32_all(float z) {
+    return fabsf(z) > 88.0f ? fmaxf(z, -0.0f) : silu_f32_fast(z);
 }
 
 // The reduced-precision paths carry every pre-activation and activation of
@@ -324,15 +327,19 @@ static_assert(kOffW3 - kOffW2 == kOffW4 - kOffW3 && kOffW2 % 4 == 0 && (kOffW3 -
 
 // NTL tiles side by side; amax (nullable): this lane's running max |h| of the
 // inputs of hidden layers 2..4, over the tiles k whose sample is real[k].
-// EXACT: the correctly rounded SiLU (calibration: the FP8 scales come from
-// these values).
-template <int NTL, bool EXACT>
+// SILU: the correctly rounded one (calibration: the FP8 scales come from these
+// values), the fast one, or the fast one for all z.
+enum SiluForm { kSiluExact, kSiluFast, kSiluAll };
+
+template <int NTL, SiluForm SILU>
 __device__ __forceinline__ void mlp_tiles_f32(const float4* frag, const float* Ps, const float (&f1)[NTL],
-                                              const float (&f2)[NTL], float (&y0)[NTL], float (&y1)[NTL],
-                                              float* amax, const bool (&real)[NTL]) {
+                                                 const float (&f2)[NTL], float (&y0)[NTL], float (&y1)[NTL],
+                                                 float* amax, const bool (&real)[NTL]) {
     const int lane = lane_id();
     const int g = lane >> 4;
-    auto silu = [](float z) { return EXACT ? silu_f32(z) : silu_f32_fast(z); };
+    auto silu = [](float z) {
+        return SILU == kSiluExact ? silu_f32(z) : (SILU == kSiluFast ? silu_f32_fast(z) : silu_f32_all(z));
+    };
     float h[NTL][16];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
@@ -405,6 +412,33 @@ __device__ __forceinline__ void mlp_tiles_f32(const float4* frag, const float* P
         q1 += __shfl_xor(q1, 32, 64);
         y0[k] = q0 + Ps[cB5];
         y1[k] = q1 + Ps[cB5 + 1];
+    }
+}
+
+// Where the fast SiLU gave a NaN for a number (in a network far from any
+// trained one), every later activation of the sample is one, and both its outputs
+// are: the wave's four tiles once more, for all z, into the lanes whose outputs
+// y0, y1 (of the lane's own sample, features f1, f2) are NaN.  Called by the whole
+// wave.
+__device__ __forceinline__ void mlp_redo_f32(const float4* frag, const float* Ps, float f1, float f2, float& y0,
+                                             float& y1) {
+    const bool redo = y0 != y0;
+    if (__builtin_expect(!any_lane(redo), 1)) return;
+    const int lane = lane_id();
+#pragma unroll 1
+    for (int tile = 0; tile < 4; ++tile) {
+        const int src = 16 * tile + (lane & 15);
+        const float g1[1] = {__shfl(f1, src, 64)}, g2[1] = {__shfl(f2, src, 64)};
+        const bool real[1] = {};
+        float o0[1], o1[1];
+        // (weights read again, not kept from the first time)
+        int opaque = 0;
+        asm volatile("" : "+s"(opaque));
+        mlp_tiles_f32<1, kSiluAll>(frag + opaque, Ps + opaque, g1, g2, o0, o1, nullptr, real);
+        if (redo && (lane >> 4) == tile) {
+            y0 = o0[0];
+            y1 = o1[0];
+        }
     }
 }
 
@@ -553,8 +587,8 @@ __device__ __forceinline__ void net_tiles(NetLds<SAMP>& s, int tile, float f1, f
         g2[k] = __shfl(f2, src, 64);
     }
     if constexpr (SAMP == CS_SAMPLER_MLP_F32) {
-        bool real[NTL] = {};
-        mlp_tiles_f32<NTL, false>(s.frag, s.P, g1, g2, y0, y1, nullptr, real);
+        const bool real[NTL] = {};
+        mlp_tiles_f32<NTL, kSiluFast>(s.frag, s.P, g1, g2, y0, y1, nullptr, real);
     } else {
         mlp_tiles<SAMP, NTL>(s.frag, s.P, s.sc, g1, g2, y0, y1);
     }
@@ -583,6 +617,7 @@ __device__ __forceinline__ float2 net_outputs(NetLds<SAMP>& s, const MlpDev& m, 
             else
                 net_tiles<SAMP, 2>(s, tile, f1, f2, out);
         }
+        if constexpr (SAMP == CS_SAMPLER_MLP_F32) mlp_redo_f32(s.frag, s.P, f1, f2, out.x, out.y);
     }
     return need ? out : make_float2(0.0f, 0.0f);
 }
