@@ -383,8 +383,9 @@ __global__ __launch_bounds__(256) void k_sample_plain(const T* __restrict__ x, c
         if ((int64_t)tid < n - piece * 256) {
             // (streamed out as they come, not left for the end-of-kernel write-back)
             __builtin_nontemporal_store((T)(1.0 - v), &(mu_out + piece * 256)[tid]);
-            __builtin_nontemporal_store((T)(sizeof(T) == 4 ? recip_approx(a) : 1.0 / a),
-                                        &(ratio_out + piece * 256)[tid]);
+            // (an infinite a has no refined estimate)
+            const double ratio = sizeof(T) == 4 ? (a > 1e300 ? 0.0 : recip_approx(a)) : 1.0 / a;
+            __builtin_nontemporal_store((T)ratio, &(ratio_out + piece * 256)[tid]);
         }
     }
 }
