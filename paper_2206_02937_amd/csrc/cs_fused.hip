@@ -126,7 +126,8 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep_scan(const PrepArgs a) {
         // this block's inclusive prefix is the total pair count T
         const int T = s_prefix + block_total;
         if (threadIdx.x == 0) a.pair_off[a.n_cells] = T;
-        const int64_t jt = ((int64_t)T + (1 << a.unit_log2) - 1) >> a.unit_log2;
+        int64_t jt = ((int64_t)T + (1 << a.unit_log2) - 1) >> a.unit_log2;
+        if (jt < 0) jt = 0;  // (the same: T may have wrapped)
         for (int64_t j = jt + threadIdx.x; j <= a.n_units; j += kPrepThreads)
             a.cell_map[j] = (int32_t)(a.n_cells - 1);
     }
