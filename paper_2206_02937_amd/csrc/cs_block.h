@@ -10,6 +10,14 @@ namespace cs {
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
+// LDS written by lanes of a wave is read by others of it from here on (a
+// wave's LDS accesses complete in order).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ int wave_inclusive_scan(int v) {
     const int lane = lane_id();
 #pragma unroll

@@ -155,14 +155,6 @@ struct FusedArgs {
     MlpDev mlp;  // network samplers only
 };
 
-// LDS written by lanes of a wave is read by others of it from here on (a
-// wave's LDS accesses complete in order).
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // The wave's step over its lanes' staged pairs e (`active` in at least one
 // lane): the plain sampler, or the network (every pair of the main stack lies
 // in the network's domain).

@@ -649,16 +649,14 @@ __global__ __launch_bounds__(kMfmaThreads, kMfmaWavesPerSimd) void k_mlp_mfma(co
         if (defer) fb[nfb + __popcll(msk & ((1ull << lane) - 1ull))] = i;
         nfb += __popcll(msk);
         // the queue's writes precede the pass's reads (one wave, in order)
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
         if (nfb >= 64) {
             fallback_pass(a, fb, 64);
             const int64_t rest = lane < nfb - 64 ? fb[64 + lane] : 0;
             __builtin_amdgcn_wave_barrier();
             if (lane < nfb - 64) fb[lane] = rest;
             nfb -= 64;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_sync();
         }
     }
     if (nfb > 0) fallback_pass(a, fb, nfb);
@@ -744,16 +742,14 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_mlp_f32(const FwdArgs a) {
         if (msk == 0) continue;
         if (defer) fb[nfb + __popcll(msk & ((1ull << lane) - 1ull))] = i;
         nfb += __popcll(msk);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
         if (nfb >= 64) {
             fallback_pass(a, fb, 64);
             const int64_t rest = lane < nfb - 64 ? fb[64 + lane] : 0;
             __builtin_amdgcn_wave_barrier();
             if (lane < nfb - 64) fb[lane] = rest;
             nfb -= 64;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_sync();
         }
     }
     if (nfb > 0) fallback_pass(a, fb, nfb);

@@ -122,9 +122,7 @@ __device__ __forceinline__ void outer_acc(floatx4_p& acc, float* sd, float* sa, 
     for (int o = 0; o < NO; ++o) sd[o * kPnetRow + lane] = d[o];
 #pragma unroll
     for (int i = 0; i < NI; ++i) sa[i * kPnetRow + lane] = a[i];
-    // (one wave: its LDS accesses complete in order)
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     const int c = lane & 15, g = lane >> 4;
     const float* pd = sd + (c < NO ? c : NO - 1) * kPnetRow + 16 * g;
     const float* pa = sa + (c < NI ? c : NI - 1) * kPnetRow + 16 * g;
@@ -150,8 +148,7 @@ __device__ __forceinline__ void outer_acc(floatx4_p& acc, float* sd, float* sa, 
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) acc[r] += s[0][r] + s[1][r];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
 }
 
 // This lane's entries of a layer's accumulated tile into the wave's partial
