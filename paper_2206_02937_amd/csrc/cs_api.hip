@@ -390,6 +390,8 @@ cs_status cs_compton_step_noalloc(cs_ctx* ctx, cs_dtype dtype, cs_species electr
     if (s != CS_OK) return s;
     void* base = static_scratch(ctx->device);
     if (!base) return fail(ctx, CS_ERR_NOT_READY, "cs_compton_step_noalloc: no static scratch on this device");
+    DeviceGuard g(ctx->device);  // (the plan depends on the device)
+    if (!g.ok) return fail(ctx, CS_ERR_HIP, "cs_compton_step_noalloc: cannot select device");
     const Plan pl = plan_step(CS_STRATEGY_FUSED, 0, 0, n_cells, electrons.n, photons.n, sampler, dtype);
     const size_t fixed = cs::ws_fixed_bytes(kStaticStatusWords);
     if (pl.status_words > kStaticStatusWords || pl.bytes > kStaticScratchBytes - fixed) {
@@ -400,8 +402,6 @@ cs_status cs_compton_step_noalloc(cs_ctx* ctx, cs_dtype dtype, cs_species electr
                       pl.bytes + fixed, kStaticScratchBytes);
         return fail(ctx, CS_ERR_UNSUPPORTED, msg);
     }
-    DeviceGuard g(ctx->device);
-    if (!g.ok) return fail(ctx, CS_ERR_HIP, "cs_compton_step_noalloc: cannot select device");
     cs::Workspace w;
     w.base = base;
     w.bytes = kStaticScratchBytes;

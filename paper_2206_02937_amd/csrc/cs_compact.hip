@@ -508,26 +508,10 @@ void carve_compact_buffers(const Workspace& w, const StepShape& s, CompactBuffer
     b->coll_fb = (int64_t*)take(8 * s.n_collide_blocks);
 }
 
-// Workgroups of k_pair_compact<T, PPL, O32> resident at once on a compute unit
-// of the current device, and its compute units; computed once.
-struct Resident {
-    int64_t per_cu, cus;
-};
-
 template <typename T, int PPL, bool O32 = true>
 static Resident pair_resident() {
-    static int64_t per_cu_cached = -1, cus_cached = -1;
-    if (per_cu_cached < 0 || cus_cached < 0) {
-        int dev = 0, n_cu = 0, per_cu = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &per_cu, reinterpret_cast<const void*>(&k_pair_compact<T, PPL, O32>), kChunk, 0) != hipSuccess)
-            return {0, 0};  // unknown: no pacing
-        per_cu_cached = per_cu;
-        cus_cached = n_cu;
-    }
-    return {per_cu_cached, cus_cached};
+    static ResidentCache cache;
+    return resident_of(cache, reinterpret_cast<const void*>(&k_pair_compact<T, PPL, O32>), kChunk);
 }
 
 template <typename T, int PPL, bool O32 = true>

@@ -563,26 +563,29 @@ hipError_t launch_prep(const StepShape& sh, StepControl* ctrl, uint64_t* status,
     return hipGetLastError();
 }
 
+Resident resident_of(ResidentCache& cache, const void* kernel, int threads) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return {0, 0};
+    return cache.get(dev, [&]() -> Resident {
+        int n_cu = 0, per_cu = 0;
+        if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess)
+            return {0, 0};
+        return {per_cu, n_cu};
+    });
+}
+
 // Workgroups of k_step<T, SAMP, true> resident at once on the current device,
 // at most kFusedMaxBlocks (what the partial sums of a small step have room
-// for), computed once.
+// for).
 constexpr int64_t kFusedMaxBlocks = 1024;
 
 template <typename T, int SAMP>
 static int64_t step_resident_blocks() {
-    static int64_t cached = -1;
-    if (cached < 0) {
-        int dev = 0, n_cu = 0, per_cu = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &per_cu, reinterpret_cast<const void*>(&k_step<T, SAMP, true>), kChunk, 0) != hipSuccess ||
-            n_cu <= 0 || per_cu <= 0)
-            return 512;  // unknown
-        const int64_t n = (int64_t)n_cu * per_cu;
-        cached = n < kFusedMaxBlocks ? n : kFusedMaxBlocks;
-    }
-    return cached;
+    static ResidentCache cache;
+    const Resident r = resident_of(cache, reinterpret_cast<const void*>(&k_step<T, SAMP, true>), kChunk);
+    const int64_t n = r.per_cu * r.cus;
+    return n <= 0 ? 512 : (n < kFusedMaxBlocks ? n : kFusedMaxBlocks);
 }
 
 template <typename T>

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "../../include/compton.h"
+#include "cs_resident.h"
 
 namespace cs {
 
@@ -119,6 +120,11 @@ struct CompactBuffers {
     double* coll_ea;      // [n_collide_blocks]
     int64_t* coll_fb;     // [n_collide_blocks]
 };
+
+// Workgroups of `threads` threads of a kernel resident at once on a compute
+// unit of the current device, and its compute units (looked up once per
+// device; {0, 0} if the runtime does not say).
+Resident resident_of(ResidentCache& cache, const void* kernel, int threads);
 
 int64_t compact_collide_threads(cs_sampler s);
 // compact: chunks per pair workgroup (a multiple of the pairs per lane, at
