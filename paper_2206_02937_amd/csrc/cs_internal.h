@@ -228,6 +228,7 @@ struct NtcState {
     int64_t cap_e = 0, cap_g = 0;
     void* host = nullptr;
     hipEvent_t ev = nullptr;
+    bool had_large = false;  // the last eager step had large cells (decides when their kernels are queued, nothing else)
 };
 enum class NtcOutcome { kOk, kLayout, kTooMany };
 hipError_t ntc_step(NtcState& s, cs_dtype dtype, const cs_species& e, const cs_species& g, const int64_t* off_e,

@@ -17,7 +17,7 @@
 //   k_ntc_count    64 or 16 lanes per cell: W, P_max, the count
 //   k_ntc_scan     the candidates before each few cells and the total, which
 //                  stays on the device, the list of the large cells (more than
-//                  kNtcLocal candidates), and whether the step proceeds (a step
+//                  ntc_local candidates), and whether the step proceeds (a step
 //                  with more candidates than the capacity fixed before it, the
 //                  context's grown one or a graph's, changes nothing and flags
 //                  its stats record)
@@ -25,8 +25,8 @@
 //                  rounds of ready candidates (evaluation, and the accepted
 //                  ones' scattering, on full waves), all state in LDS, until
 //                  none is left
-//   the large cells (none of these is queued by an eager step that has no
-//   such cell; in a graph they find an empty list):
+//   the large cells (an eager step that has no such cell, after one that had
+//   none, queues none of these; in a graph they find an empty list):
 //   k_ntc_pick     a workgroup per cell: its candidates' electrons, photons and
 //                  acceptance uniforms; every candidate registers for round 0
 //                  in the particles' "first toucher" words (atomicMax of
@@ -82,7 +82,7 @@ constexpr int kNtcScanPer = 4;                            // cells per thread in
 constexpr int kNtcScanBlock = kNtcThreads * kNtcScanPer;  // cells per scan workgroup
 constexpr int kNtcPiece = 16;                             // cells per piece: 64 pieces per scan workgroup
 static_assert(kNtcScanBlock == 64 * kNtcPiece, "a wave reads a scan workgroup's pieces at once");
-constexpr int kNtcLocal = 256;                              // candidates of a cell that k_ntc_cells takes
+constexpr int kNtcLocalMax = 256;                           // candidates of a cell that k_ntc_cells takes, at most
 constexpr int kNtcRedPer = 2;                               // candidates per thread in the reduction
 constexpr int64_t kNtcMaxCand = 2147483647;                 // candidates per step: below 2^31 - 1
 
@@ -92,12 +92,12 @@ constexpr int64_t kNtcMaxCand = 2147483647;                 // candidates per st
 // whatever the cell count).
 struct NtcCtl {
     long long total;    // candidates of the step
-    long long total_l;  // those in cells of more than kNtcLocal
+    long long total_l;  // those in the large cells
     int32_t layout_bad;
     int32_t too_many;   // 2^31 - 1 or more candidates
     int32_t overflow;   // more candidates than the launches were sized for
     int32_t go;         // none of the above: the step proceeds
-    uint32_t n_large;   // cells of more than kNtcLocal candidates
+    uint32_t n_large;   // the large cells
     uint32_t n_pend;    // cells left to k_ntc_serial
     uint32_t done;      // workgroups of k_ntc_scan that have finished
     uint32_t pad;
@@ -127,6 +127,7 @@ struct NtcArgs {
     Particles<T> pt;
     const int64_t *off_e, *off_g;
     int64_t n_cells;
+    int64_t local;   // candidates of a cell up to which it is not a large one
     int64_t total;   // candidates of the large cells; filled on the device by ntc_live
     double dt, dn;
     uint64_t seed, step;  // step: the host's, or the device word's (dev_step)
@@ -279,8 +280,8 @@ __global__ __launch_bounds__(kNtcThreads) void k_ntc_count(const T* ew, const T*
 // layout, fewer than 2^31 - 1 candidates, at most `cap` of them).  When the tag
 // epoch is about to wrap, it clears the touch words and restarts the epoch at
 // 0.  With `host` set the control words go there too.
-__global__ __launch_bounds__(kNtcThreads) void k_ntc_scan(const int64_t* count, int64_t n_cells, int2* piece,
-                                                        long long* bsum, int32_t* large, int64_t cap,
+__global__ __launch_bounds__(kNtcThreads) void k_ntc_scan(const int64_t* count, int64_t n_cells, int64_t local,
+                                                        int2* piece, long long* bsum, int32_t* large, int64_t cap,
                                                         NtcCtl* ctl, NtcHead* head, unsigned long long* touch,
                                                         int64_t n_touch, NtcCtl* host) {
     __shared__ long long s[kNtcThreads / 64];
@@ -296,7 +297,7 @@ __global__ __launch_bounds__(kNtcThreads) void k_ntc_scan(const int64_t* count, 
     for (int q = 0; q < kNtcScanPer; ++q) {
         if (v[q] < 0) {
             marks |= v[q] == kNtcBadLayout ? 2 : 1;
-        } else if (v[q] <= kNtcLocal) {
+        } else if (v[q] <= local) {
             small += v[q];
         } else {
             lots += v[q];
@@ -433,7 +434,7 @@ __global__ __launch_bounds__(kNtcThreads) void k_ntc_pick(const NtcArgs<T> a_in)
         // the large cells' candidates before this cell's
         const int64_t cp = c / kNtcPiece * kNtcPiece;
         long long v = lane < (int)(c - cp) ? a.count[cp + lane] : 0;
-        v = v > kNtcLocal ? v : 0;
+        v = v > a.local ? v : 0;
 #pragma unroll
         for (int o = kNtcPiece / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
         const int64_t j0 = a.bsum[2 * (c / kNtcScanBlock) + 1] + a.piece[c / kNtcPiece].y + __shfl(v, 0, 64);
@@ -555,7 +556,7 @@ __device__ __forceinline__ void ntc_collide(const NtcArgs<T>& a, int64_t j, int3
 // the next round (the earliest open one of all is ready in every round, so that
 // the rounds end).
 constexpr int kNtcWin = 256;
-static_assert(kNtcLocal <= kNtcWin && kNtcWin <= 256, "8-bit indices of a window");
+static_assert(kNtcLocalMax <= kNtcWin && kNtcWin <= 256, "8-bit indices of a window");
 
 template <typename T>
 struct NtcWindow {
@@ -681,7 +682,7 @@ __device__ __forceinline__ const NtcArgs<T>* ntc_own_args() {
     return (const NtcArgs<T>*)p;
 }
 
-// The cells of at most kNtcLocal candidates, one wave per group of consecutive
+// The cells of at most a.local candidates, one wave per group of consecutive
 // cells: those whose first candidate is among the group's share of the small
 // cells' candidates (the share follows from the step's totals alone, so that
 // eager steps and graphs of any capacity add their sums in the same order; by
@@ -746,7 +747,7 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_ntc_cells(const 
         for (int64_t cb = (64 * b_lo + p) * kNtcPiece; cb < a.n_cells && before < w1; cb += 64) {
             const int64_t c = cb + lane;
             const long long nn = c < a.n_cells ? a.count[c] : 0;
-            const int n = nn <= kNtcLocal ? (int)nn : 0;
+            const int n = nn <= a.local ? (int)nn : 0;
             int inc = n;
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
@@ -1111,6 +1112,17 @@ __global__ void k_ntc_stats_layout(cs_stats* stats) {
 // ---------------------------------------------------------------------------
 static inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
+// Candidates of a cell up to which one wave resolves it (k_ntc_cells).  A wave
+// takes its 64s in turn, the kernels of the large cells take all at once over
+// the chip, in seven launches more: the fewer the cells, the sooner these are
+// shorter.  Whole step, us, by waves / by the launches (cells x candidates): 2 x 167
+// 71 / 52, 10 x 167 75 / 67, 131 x 222 105 / 82, 455 x 255 115 / 99, but 16 x 111
+// 55 / 68, 699 x 167 86 / 100, 1823 x 255 163 / 190.  (By the cell count alone,
+// so that an eager step and a graph resolve a cell the same way.)
+static int64_t ntc_local(int64_t n_cells) {
+    return n_cells < 8 ? 64 : (n_cells < 640 ? 128 : (n_cells < 1280 ? 192 : kNtcLocalMax));
+}
+
 // Device scratch of a step, laid out from sizes the host knows before the
 // step: the cell count, the candidate capacity and the particle counts.
 struct NtcLayout {
@@ -1123,8 +1135,8 @@ static NtcLayout ntc_layout(int64_t n_cells, int64_t cap) {
     NtcLayout l;
     l.nb = (n_cells + kNtcScanBlock - 1) / kNtcScanBlock;
     if (l.nb < 1) l.nb = 1;  // (a step without cells too)
-    // (a share has at least 16 candidates, a small cell at most kNtcLocal)
-    constexpr int64_t kSharesPerCell = kNtcLocal / 16;
+    // (a small cell has at most kNtcLocalMax candidates, a share about 16 or more)
+    constexpr int64_t kSharesPerCell = kNtcLocalMax / 16;
     l.n_cell = n_cells < kNtcCellBlocks / kSharesPerCell ? n_cells * kSharesPerCell : kNtcCellBlocks;
     l.n_pb = n_cells < 2048 ? n_cells : 2048;
     l.n_seg = (cap + kNtcSeg - 1) / kNtcSeg;
@@ -1265,8 +1277,9 @@ struct NtcQueue {
                 (const T*)e.w, (const T*)g.w, off_e, off_g, n_cells, e.n, g.n, dt, dn, seed, step, head,
                 dev_step ? 1 : 0, count, p_max, pending);
         }
-        k_ntc_scan<<<(unsigned)l.nb, kNtcThreads, 0, st>>>(count, n_cells, piece, bsum, large, cap, ctl, head, touch,
-                                                           2 * (s.cap_e + s.cap_g), (NtcCtl*)host);
+        a.local = ntc_local(n_cells);
+        k_ntc_scan<<<(unsigned)l.nb, kNtcThreads, 0, st>>>(count, n_cells, a.local, piece, bsum, large, cap, ctl, head,
+                                                           touch, 2 * (s.cap_e + s.cap_g), (NtcCtl*)host);
         if (host) {
             const hipError_t err = hipEventRecord(ev, st);
             if (err != hipSuccess) return err;
@@ -1321,7 +1334,7 @@ struct NtcQueue {
     }
 
     void large() {
-        if (a.n_cells <= 0 || cap <= kNtcLocal) return;  // (no cell can have more than the capacity)
+        if (a.n_cells <= 0 || cap <= a.local) return;  // (no cell can have more than the capacity)
         k_ntc_pick<T><<<(unsigned)l.n_pb, kNtcThreads, 0, st>>>(a);
         // one workgroup per segment, up to the capacity; kNtcSub smaller ones per segment
         k_ntc_eval<T><<<(unsigned)l.n_seg, kNtcSeg, 0, st>>>(a);
@@ -1367,15 +1380,20 @@ static hipError_t ntc_launch(NtcState& s, const cs_species& e, const cs_species&
     }
     // The counts and the small cells are queued at once; the host then waits
     // only for the counts' control words (the small cells run meanwhile) and
-    // queues the large cells if there are any.  A step with more candidates
-    // than the capacity changed nothing: the scratch grows and the step is
-    // queued again (same inputs, same candidates).
+    // queues the large cells if there are any (or does so before it waits, if
+    // the step before had some: their kernels leave where there are none, and
+    // the chip does not idle meanwhile).  A step with more candidates than the
+    // capacity changed nothing: the scratch grows and the step is queued again
+    // (same inputs, same candidates).
     NtcQueue<T> q;
     err = q.start(s, e, g, off_e, off_g, n_cells, dt, dn, seed, step, false, st, s.host, s.ev);
+    const bool ahead = s.had_large;
+    if (err == hipSuccess && ahead) q.large();
     if (err == hipSuccess) err = hipEventSynchronize(s.ev);
     if (err != hipSuccess) return err;
     const NtcCtl h = *(const NtcCtl*)s.host;
-    if (h.go && h.total_l > 0) q.large();
+    s.had_large = h.total_l > 0;
+    if (h.go && h.total_l > 0 && !ahead) q.large();
     err = q.finish(stats);
     if (err != hipSuccess) return err;
     if (h.layout_bad) {
