@@ -214,37 +214,68 @@ __device__ __forceinline__ long long block_excl_scan64(long long v, long long* l
 // candidates.
 constexpr long long kNtcBadCount = -1, kNtcBadLayout = -2;
 
+// The largest finite non-negative weight of electrons [e0, e0 + nec) and
+// photons [g0, g0 + ngc) (both not empty) that lane l of `n` finds (a maximum does
+// not depend on the order; past a species' end its first weight is read again).
+template <typename T>
+__device__ __forceinline__ T ntc_largest_weight(const T* ew, const T* gw, int64_t e0, int64_t nec, int64_t g0,
+                                                int64_t ngc, int l, int n) {
+    T w = (T)0;
+    const int64_t most = nec > ngc ? nec : ngc;
+    for (int64_t b = 0; b < most; b += 4 * n) {
+        T v[8];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t i = b + n * q + l;
+            v[q] = ew[e0 + (i < nec ? i : 0)];
+            v[4 + q] = gw[g0 + (i < ngc ? i : 0)];
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) w = isfinite(v[q]) && v[q] > w ? v[q] : w;
+    }
+    return w;
+}
+
 // L lanes per cell: the largest valid weight, the bound and the candidate
-// count; bound by reading the weights once (8 per lane in flight).
+// count; bound by reading the weights once (8 per lane in flight).  With 16
+// lanes per cell, cells of kNtcCountLong of a species or more are read by the whole
+// wave, one after another (100000 cells of 16 and one of a million: the step
+// 8.6 ms without, 4.3 ms so).
+constexpr uint32_t kNtcCountLong = 512;
+
 template <typename T, int L>
 __global__ __launch_bounds__(kNtcThreads) void k_ntc_count(const T* ew, const T* gw, const int64_t* off_e,
                                                          const int64_t* off_g, int64_t n_cells, int64_t ne,
                                                          int64_t ng, double dt, double dn, uint64_t seed,
                                                          uint64_t step_host, const NtcHead* head, int dev_step,
                                                          int64_t* count, double* p_max, int32_t* pending) {
+    static_assert(L == 16 || L == 64, "lanes of a cell");
     const int l = lane_id() & (L - 1);
     const int64_t c = ((int64_t)blockIdx.x * kNtcThreads + threadIdx.x) / L;
-    if (c >= n_cells) return;
+    if (c >= n_cells) return;  // (whole cells, the last ones of the last workgroup)
     const uint64_t step = dev_step ? head->step : step_host;
     const int64_t e0 = off_e[c], e1 = off_e[c + 1], g0 = off_g[c], g1 = off_g[c + 1];
     const bool bad = e0 < 0 || e1 < e0 || e1 > ne || g0 < 0 || g1 < g0 || g1 > ng ||
                      (c == 0 && (e0 != 0 || g0 != 0)) || (c == n_cells - 1 && (e1 != ne || g1 != ng));
     const int64_t nec = bad ? 0 : e1 - e0, ngc = bad ? 0 : g1 - g0;
-    // largest finite non-negative weight (a maximum does not depend on the
-    // order; past a species' end its first weight is read again)
     T w = (T)0;
-    if (nec > 0 && ngc > 0) {
-        const int64_t most = nec > ngc ? nec : ngc;
-        for (int64_t b = 0; b < most; b += 4 * L) {
-            T v[8];
+    const bool is_long = L < 64 && ((uint32_t)nec | (uint32_t)ngc) >= kNtcCountLong;
+    if (nec > 0 && ngc > 0 && !is_long) w = ntc_largest_weight(ew, gw, e0, nec, g0, ngc, l, L);
+    if (L < 64 && any_lane(is_long)) {
+        const int n = __popcll(lanes(true));  // (the lanes of the wave's cells)
+        for (uint64_t m = lanes(is_long && l == 0 && nec > 0 && ngc > 0); m; m &= m - 1) {
+            const int src = (int)__ffsll((unsigned long long)m) - 1;  // the cell's first lane
+            T v = ntc_largest_weight(ew, gw, __shfl((long long)e0, src, 64), __shfl((long long)nec, src, 64),
+                                     __shfl((long long)g0, src, 64), __shfl((long long)ngc, src, 64), lane_id(), n);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int64_t i = b + L * q + l;
-                v[q] = ew[e0 + (i < nec ? i : 0)];
-                v[4 + q] = gw[g0 + (i < ngc ? i : 0)];
+            for (int o = L / 2; o > 0; o >>= 1) {
+                const T x = __shfl_xor(v, o, 64);
+                v = x > v ? x : v;
             }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) w = isfinite(v[q]) && v[q] > w ? v[q] : w;
+            for (int o = 0; o < n; o += L) {
+                const T x = __shfl(v, o, 64);
+                if (lane_id() - l == src) w = x > w ? x : w;
+            }
         }
     }
 #pragma unroll

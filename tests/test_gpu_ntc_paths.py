@@ -1,8 +1,8 @@
 """Which way the no-time-counter step takes a cell: one wave up to a number of
 candidates that falls with the cell count, the kernels of the large cells
-beyond, queued before or after the counts are known.  Against the FP64 oracle
-element by element, with the metric and tolerances of the no-time-counter
-tests."""
+beyond, queued before or after the counts are known; and the largest weight of
+cells far longer than the average.  Against the FP64 oracle element by element,
+with the metric and tolerances of the no-time-counter tests."""
 import numpy as np
 import pytest
 
@@ -25,6 +25,27 @@ def test_cells_at_the_limit(ctx, orc, n_cells, local):  # noqa: F811
     for st, gst, diag in _chain_compare(ctx, orc, p, [0, 1]):
         assert np.array_equal(np.bincount(diag["cell"], minlength=n_cells), ne * ng)
         assert st["n_collided"] > 0
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n_cells, where", [(197, 0), (197, 77), (197, 196), (196, 195), (199, 198), (198, 196)])
+def test_largest_weight_of_long_cells(ctx, orc, dtype, n_cells, where):  # noqa: F811
+    """Cells of 2 and one of 511 to 3000 (16 lanes share out a cell, the whole
+    wave a long one, also in the last wave, which has fewer cells): its one heavy
+    particle, anywhere in it, sets its bound."""
+    for n_long, heavy_at, species in ((511, 510, "e"), (512, 0, "g"), (3000, 2999, "e"), (2950, 1234, "g")):
+        n = np.full(n_cells, 2)
+        n[where] = n_long
+        p = _cells_plasma(n, n, 0.002, 5)
+        w = p.e["w"] if species == "e" else p.g["w"]
+        w[p.off_e[where] + heavy_at] = 8.0
+        for d in (p.e, p.g):
+            for k in d:
+                d[k] = d[k].astype(dtype)
+        assert n.sum() <= 32 * n_cells
+        (st, gst, diag), = _chain_compare(ctx, orc, p, [3])
+        want = 0.002 * 8.0 * n_long ** 2
+        assert abs(np.sum(diag["cell"] == where) - want) <= 1.0
 
 
 def test_large_cells_come_and_go():
