@@ -16,8 +16,8 @@
 // shares a particle with it gives the sequential result.  The step:
 //   k_ntc_count    64 or 16 lanes per cell: W, P_max, the count
 //   k_ntc_scan     the candidates before each few cells and the total, which
-//                  stays on the device, the list of the large cells (more than
-//                  ntc_local candidates), and whether the step proceeds (a step
+//                  stays on the device, which cells are large ones and the
+//                  list of them (see kNtcLow), and whether the step proceeds (a step
 //                  with more candidates than the capacity fixed before it, the
 //                  context's grown one or a graph's, changes nothing and flags
 //                  its stats record)
@@ -82,7 +82,21 @@ constexpr int kNtcScanPer = 4;                            // cells per thread in
 constexpr int kNtcScanBlock = kNtcThreads * kNtcScanPer;  // cells per scan workgroup
 constexpr int kNtcPiece = 16;                             // cells per piece: 64 pieces per scan workgroup
 static_assert(kNtcScanBlock == 64 * kNtcPiece, "a wave reads a scan workgroup's pieces at once");
-constexpr int kNtcLocalMax = 256;                           // candidates of a cell that k_ntc_cells takes, at most
+// Which cells are resolved by one wave each (k_ntc_cells), which by the kernels
+// of the large cells.  A wave takes a cell's candidates 64 at a time in turn, those
+// kernels take all at once over the chip, in seven launches more.  Up to kNtcLow
+// candidates a wave is the quicker, beyond kNtcMidMax it has no room.  The cells
+// between go to waves if there are kNtcMidMin of them, which keep the chip busy
+// (whole step, us, by waves / by the launches, cells x candidates: 455 x 255 115
+// / 99, 699 x 167 86 / 100, 1823 x 255 163 / 190), or if none has more than
+// kNtcMidHigh and the launches are not needed for others either (16 x 111 55 /
+// 68, but 2 x 167 71 / 52; 6956 cells of a few candidates and denser ones up to 330
+// 185 / 119), and there are not fewer cells than kNtcFew (4 x 111 64 / 52 in a
+// graph).  Where the launches are needed and all cells together are fewer than
+// kNtcMidMin, they take every cell (100 x 35 and 4 denser ones: 107 -> 92).  By the
+// candidates alone, so that an eager step and a graph resolve a cell the same way.
+constexpr int kNtcLow = 64, kNtcMidHigh = 128, kNtcMidMax = 256;
+constexpr int kNtcMidMin = 640, kNtcFew = 8;
 constexpr int kNtcRedPer = 2;                               // candidates per thread in the reduction
 constexpr int64_t kNtcMaxCand = 2147483647;                 // candidates per step: below 2^31 - 1
 
@@ -97,9 +111,13 @@ struct NtcCtl {
     int32_t too_many;   // 2^31 - 1 or more candidates
     int32_t overflow;   // more candidates than the launches were sized for
     int32_t go;         // none of the above: the step proceeds
-    uint32_t n_large;   // the large cells
+    uint32_t n_large;   // large cells (all cells where local is 0)
+    uint32_t n_over;    // cells of more than kNtcMidMax candidates
+    uint32_t n_mid;     // cells of more than kNtcLow, up to kNtcMidMax
+    uint32_t n_high;    // those of them of more than kNtcMidHigh
     uint32_t n_pend;    // cells left to k_ntc_serial
     uint32_t done;      // workgroups of k_ntc_scan that have finished
+    int32_t local;      // candidates of a cell up to which it is not a large one
     uint32_t pad;
 };
 // Candidates per segment: the evaluation kernel takes one segment per
@@ -127,7 +145,6 @@ struct NtcArgs {
     Particles<T> pt;
     const int64_t *off_e, *off_g;
     int64_t n_cells;
-    int64_t local;   // candidates of a cell up to which it is not a large one
     int64_t total;   // candidates of the large cells; filled on the device by ntc_live
     double dt, dn;
     uint64_t seed, step;  // step: the host's, or the device word's (dev_step)
@@ -140,10 +157,12 @@ struct NtcArgs {
     const double* p_max;      // [n_cells]
     int32_t *c_ie, *c_ig, *c_cell, *c_local;
     double* c_u;              // acceptance uniform of each candidate
-    const long long* bsum;    // [2 b], [2 b + 1]: small and large cells' candidates before scan workgroup b
+    const long long* bsum;    // [3 b], [3 b + 1]: small and large cells' candidates before scan workgroup b
     int64_t n_bsum;           // scan workgroups
-    const int2* piece;        // the same (x, y) of each piece of kNtcPiece cells, within its scan workgroup
-    const int32_t* large;     // the large cells, in no particular order
+    const int4* piece;        // per piece of kNtcPiece cells the candidates before it within its scan workgroup, in
+                              // cells up to the low limit (x), between the limits (y), beyond (z)
+    const int32_t* large;     // [n_cells] in no particular order: cells beyond the upper limit from the start on,
+                              // those between the limits from the end back
     int32_t* pend;            // the cells left to k_ntc_serial, likewise
     uint8_t* status;  // bit 0 resolved; 2 collided, 4 invalid, 8 P > P_max
     double *r_ratio, *r_eb, *r_ea;
@@ -305,21 +324,22 @@ __global__ __launch_bounds__(kNtcThreads) void k_ntc_count(const T* ew, const T*
     }
 }
 
-// The small and the large cells' candidates before each piece of cells, the
-// list of the large cells, and, by the workgroup that finishes last, those
-// before each workgroup and the totals, and whether the step proceeds (a valid
-// layout, fewer than 2^31 - 1 candidates, at most `cap` of them).  When the tag
-// epoch is about to wrap, it clears the touch words and restarts the epoch at
-// 0.  With `host` set the control words go there too.
-__global__ __launch_bounds__(kNtcThreads) void k_ntc_scan(const int64_t* count, int64_t n_cells, int64_t local,
-                                                        int2* piece, long long* bsum, int32_t* large, int64_t cap,
+// The candidates before each piece of cells, the lists of the cells beyond the
+// limits, and, by the workgroup that finishes last, which of them are large ones,
+// the small and the large cells' candidates before each workgroup, the totals, and
+// whether the step proceeds (a valid layout, fewer than 2^31 - 1 candidates, at
+// most `cap` of them).  When the tag epoch is about to wrap, it clears the touch
+// words and restarts the epoch at 0.  With `host` set the control words go there
+// too.
+__global__ __launch_bounds__(kNtcThreads) void k_ntc_scan(const int64_t* count, int64_t n_cells, int4* piece,
+                                                        long long* bsum, int32_t* large, int64_t cap,
                                                         NtcCtl* ctl, NtcHead* head, unsigned long long* touch,
                                                         int64_t n_touch, NtcCtl* host) {
     __shared__ long long s[kNtcThreads / 64];
     __shared__ int s_last;
     constexpr long long kBadCount = 1ll << 60, kBadLayout = 1ll << 61;  // marks in a workgroup's word
     const int64_t base = (int64_t)blockIdx.x * kNtcScanBlock + (int64_t)threadIdx.x * kNtcScanPer;
-    long long small = 0, lots = 0;
+    long long small = 0, lots = 0;  // small: cells up to the low limit, and those between the limits 32 bits up
     int marks = 0;
     int64_t v[kNtcScanPer];
 #pragma unroll
@@ -328,49 +348,65 @@ __global__ __launch_bounds__(kNtcThreads) void k_ntc_scan(const int64_t* count, 
     for (int q = 0; q < kNtcScanPer; ++q) {
         if (v[q] < 0) {
             marks |= v[q] == kNtcBadLayout ? 2 : 1;
-        } else if (v[q] <= local) {
+        } else if (v[q] <= kNtcLow) {
             small += v[q];
+        } else if (v[q] <= kNtcMidMax) {
+            small += (long long)v[q] << 32;
+            if (v[q] > kNtcMidHigh) atomicAdd(&ctl->n_high, 1u);
+            large[n_cells - 1 - atomicAdd(&ctl->n_mid, 1u)] = (int32_t)(base + q);
         } else {
             lots += v[q];
-            large[atomicAdd(&ctl->n_large, 1u)] = (int32_t)(base + q);
+            large[atomicAdd(&ctl->n_over, 1u)] = (int32_t)(base + q);
         }
     }
     long long sum_s, sum_l;
     const long long ex_s = block_excl_scan64<kNtcThreads>(small, s, &sum_s);
     const long long ex_l = block_excl_scan64<kNtcThreads>(lots, s, &sum_l);
     if (base % kNtcPiece == 0 && base < n_cells)
-        piece[base / kNtcPiece] = make_int2((int)ex_s, ex_l < kNtcMaxCand ? (int)ex_l : 0);  // (else too many in all)
+        piece[base / kNtcPiece] = make_int4((int)ex_s, (int)(ex_s >> 32),
+                                            ex_l < kNtcMaxCand ? (int)ex_l : 0, 0);  // (else too many in all)
     const bool bad_c = __syncthreads_or(marks & 1), bad_l = __syncthreads_or(marks & 2);
     if (threadIdx.x == 0) {
-        // the two words, past every cache, before the ticket (they are all
+        // the three words, past every cache, before the ticket (they are all
         // that the last workgroup reads of this one, so that no cache has to
         // be written back for it)
-        const long long w = sum_s | (bad_c ? kBadCount : 0) | (bad_l ? kBadLayout : 0);
-        __hip_atomic_store(&bsum[2 * (int64_t)blockIdx.x], w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&bsum[2 * (int64_t)blockIdx.x + 1], sum_l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const long long w = (sum_s & 0xFFFFFFFFll) | (bad_c ? kBadCount : 0) | (bad_l ? kBadLayout : 0);
+        long long* mine = bsum + 3 * (int64_t)blockIdx.x;
+        __hip_atomic_store(&mine[0], w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&mine[1], sum_s >> 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&mine[2], sum_l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         const uint32_t before = __hip_atomic_fetch_add(&ctl->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s_last = before == gridDim.x - 1 ? 1 : 0;
     }
     __syncthreads();
     if (!s_last) return;  // (uniform in the workgroup)
+    const uint32_t n_mid = __hip_atomic_load(&ctl->n_mid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t n_over = __hip_atomic_load(&ctl->n_over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t n_high = __hip_atomic_load(&ctl->n_high, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool launches = n_over + n_high > 0 || (n_cells < kNtcFew && n_mid > 0);
+    const int local = !launches || n_mid >= kNtcMidMin ? kNtcMidMax : (n_cells < kNtcMidMin ? 0 : kNtcLow);
     const int64_t n_blocks = gridDim.x;
     long long total_s = 0, total_l = 0;
     bool bad_layout = false, bad_count = false;
     for (int64_t b0 = 0; b0 < n_blocks; b0 += kNtcThreads) {
         const int64_t b = b0 + threadIdx.x;
-        long long ws = 0, wl = 0, sum;
+        long long ws = 0, wm = 0, wl = 0, sum;
         if (b < n_blocks) {
-            ws = __hip_atomic_load(&bsum[2 * b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            wl = __hip_atomic_load(&bsum[2 * b + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            ws = __hip_atomic_load(&bsum[3 * b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            wm = __hip_atomic_load(&bsum[3 * b + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            wl = __hip_atomic_load(&bsum[3 * b + 2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         bad_layout = __syncthreads_or((ws & kBadLayout) != 0) || bad_layout;
         bad_count = __syncthreads_or((ws & kBadCount) != 0) || bad_count;
-        const long long bs = block_excl_scan64<kNtcThreads>(ws & (kBadCount - 1), s, &sum);
-        if (b < n_blocks) bsum[2 * b] = total_s + bs;
+        ws &= kBadCount - 1;
+        const long long bs = block_excl_scan64<kNtcThreads>(
+            (local >= kNtcLow ? ws : 0) + (local >= kNtcMidMax ? wm : 0), s, &sum);
+        if (b < n_blocks) bsum[3 * b] = total_s + bs;
         total_s += sum;
-        const long long bl = block_excl_scan64<kNtcThreads>(wl, s, &sum);
-        if (b < n_blocks) bsum[2 * b + 1] = total_l + bl;
+        const long long bl = block_excl_scan64<kNtcThreads>(
+            wl + (local < kNtcMidMax ? wm : 0) + (local < kNtcLow ? ws : 0), s, &sum);
+        if (b < n_blocks) bsum[3 * b + 1] = total_l + bl;
         total_l += sum;
     }
     const bool wrap = head->epoch > 0xFFFFFFFFu - 2 * kNtcRounds;  // (uniform)
@@ -388,7 +424,11 @@ __global__ __launch_bounds__(kNtcThreads) void k_ntc_scan(const int64_t* count, 
         z.too_many = bad_count || total >= kNtcMaxCand ? 1 : 0;
         z.overflow = total > cap ? 1 : 0;
         z.go = (z.layout_bad | z.too_many | z.overflow) ? 0 : 1;
-        z.n_large = __hip_atomic_load(&ctl->n_large, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        z.n_large = local == 0 ? (uint32_t)n_cells : n_over + (local < kNtcMidMax ? n_mid : 0);
+        z.n_over = n_over;
+        z.n_mid = n_mid;
+        z.n_high = n_high;
+        z.local = local;
         *ctl = z;
         if (host) *host = z;
     }
@@ -457,18 +497,22 @@ __device__ __forceinline__ int block_slot(bool take, int* lds, int* total) {
 template <typename T>
 __global__ __launch_bounds__(kNtcThreads) void k_ntc_pick(const NtcArgs<T> a_in) {
     if (!a_in.ctl->go) return;  // (uniform) the step does not proceed
-    const uint32_t n_large = a_in.ctl->n_large;
+    const uint32_t n_large = a_in.ctl->n_large, n_over = a_in.ctl->n_over;
+    const int local = a_in.ctl->local;
     const NtcArgs<T> a = ntc_live(a_in);
     const int lane = lane_id();
     for (uint32_t i = blockIdx.x; i < n_large; i += gridDim.x) {
-        const int64_t c = a.large[i], n = a.count[c];
+        const int64_t c = local == 0 ? (int64_t)i : a.large[i < n_over ? (int64_t)i : a.n_cells - 1 - (i - n_over)];
+        const int64_t n = a.count[c];
         // the large cells' candidates before this cell's
         const int64_t cp = c / kNtcPiece * kNtcPiece;
         long long v = lane < (int)(c - cp) ? a.count[cp + lane] : 0;
-        v = v > a.local ? v : 0;
+        v = v > local ? v : 0;
 #pragma unroll
         for (int o = kNtcPiece / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        const int64_t j0 = a.bsum[2 * (c / kNtcScanBlock) + 1] + a.piece[c / kNtcPiece].y + __shfl(v, 0, 64);
+        const int4 pc = a.piece[c / kNtcPiece];
+        const int64_t j0 = a.bsum[3 * (c / kNtcScanBlock) + 1] + pc.z + (local < kNtcMidMax ? pc.y : 0) +
+                           (local < kNtcLow ? pc.x : 0) + __shfl(v, 0, 64);
         const int64_t e0 = a.off_e[c], e1 = a.off_e[c + 1], g0 = a.off_g[c], g1 = a.off_g[c + 1];
         if (threadIdx.x == 0) a.cand_full[c] = j0;
         const uint64_t nec = (uint64_t)(e1 - e0), ngc = (uint64_t)(g1 - g0);
@@ -587,7 +631,7 @@ __device__ __forceinline__ void ntc_collide(const NtcArgs<T>& a, int64_t j, int3
 // the next round (the earliest open one of all is ready in every round, so that
 // the rounds end).
 constexpr int kNtcWin = 256;
-static_assert(kNtcLocalMax <= kNtcWin && kNtcWin <= 256, "8-bit indices of a window");
+static_assert(kNtcMidMax <= kNtcWin && kNtcWin <= 256, "8-bit indices of a window");
 
 template <typename T>
 struct NtcWindow {
@@ -713,7 +757,7 @@ __device__ __forceinline__ const NtcArgs<T>* ntc_own_args() {
     return (const NtcArgs<T>*)p;
 }
 
-// The cells of at most a.local candidates, one wave per group of consecutive
+// The small cells, one wave per group of consecutive
 // cells: those whose first candidate is among the group's share of the small
 // cells' candidates (the share follows from the step's totals alone, so that
 // eager steps and graphs of any capacity add their sums in the same order; by
@@ -742,6 +786,7 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_ntc_cells(const 
     const auto own = [] { return ntc_own_args<T>(); };
     const NtcArgs<T>& a = *own();
     const long long total_s = a.ctl->total - a.ctl->total_l;
+    const int local = a.ctl->local;
     if (!a.ctl->go) return;  // (uniform) the step does not proceed
     // a share of kNtcShare candidates, less where the chip would be left idle;
     // cells of more than half a share get one each, lest some waves take two
@@ -763,13 +808,14 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_ntc_cells(const 
         int64_t b_lo = 0, b_n = a.n_bsum;  // it is one of [b_lo, b_lo + b_n)
         while (b_n > 1) {
             const int64_t stride = (b_n + 63) / 64, b = b_lo + lane * stride;
-            const int k = __popcll(lanes(b < b_lo + b_n && a.bsum[2 * (b < b_lo + b_n ? b : b_lo)] <= w0)) - 1;
+            const int k = __popcll(lanes(b < b_lo + b_n && a.bsum[3 * (b < b_lo + b_n ? b : b_lo)] <= w0)) - 1;
             b_n = b_n - k * stride < stride ? b_n - k * stride : stride;
             b_lo += k * stride;
         }
-        long long before = a.bsum[2 * b_lo];
+        long long before = a.bsum[3 * b_lo];
         const int64_t n_pieces = (a.n_cells + kNtcPiece - 1) / kNtcPiece, p_l = 64 * b_lo + lane;
-        const int in_block = a.piece[p_l < n_pieces ? p_l : 64 * b_lo].x;
+        const int4 pc = a.piece[p_l < n_pieces ? p_l : 64 * b_lo];
+        const int in_block = pc.x + (local >= kNtcMidMax ? pc.y : 0);
         const int p = __popcll(lanes(p_l < n_pieces && before + in_block <= w0)) - 1;
         before += __builtin_amdgcn_readlane(in_block, p);
         // the group's cells, 64 cells at a time
@@ -778,7 +824,7 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 4 : 3) void k_ntc_cells(const 
         for (int64_t cb = (64 * b_lo + p) * kNtcPiece; cb < a.n_cells && before < w1; cb += 64) {
             const int64_t c = cb + lane;
             const long long nn = c < a.n_cells ? a.count[c] : 0;
-            const int n = nn <= a.local ? (int)nn : 0;
+            const int n = nn <= local ? (int)nn : 0;
             int inc = n;
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
@@ -1143,17 +1189,6 @@ __global__ void k_ntc_stats_layout(cs_stats* stats) {
 // ---------------------------------------------------------------------------
 static inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// Candidates of a cell up to which one wave resolves it (k_ntc_cells).  A wave
-// takes its 64s in turn, the kernels of the large cells take all at once over
-// the chip, in seven launches more: the fewer the cells, the sooner these are
-// shorter.  Whole step, us, by waves / by the launches (cells x candidates): 2 x 167
-// 71 / 52, 10 x 167 75 / 67, 131 x 222 105 / 82, 455 x 255 115 / 99, but 16 x 111
-// 55 / 68, 699 x 167 86 / 100, 1823 x 255 163 / 190.  (By the cell count alone,
-// so that an eager step and a graph resolve a cell the same way.)
-static int64_t ntc_local(int64_t n_cells) {
-    return n_cells < 8 ? 64 : (n_cells < 640 ? 128 : (n_cells < 1280 ? 192 : kNtcLocalMax));
-}
-
 // Device scratch of a step, laid out from sizes the host knows before the
 // step: the cell count, the candidate capacity and the particle counts.
 struct NtcLayout {
@@ -1166,8 +1201,8 @@ static NtcLayout ntc_layout(int64_t n_cells, int64_t cap) {
     NtcLayout l;
     l.nb = (n_cells + kNtcScanBlock - 1) / kNtcScanBlock;
     if (l.nb < 1) l.nb = 1;  // (a step without cells too)
-    // (a small cell has at most kNtcLocalMax candidates, a share about 16 or more)
-    constexpr int64_t kSharesPerCell = kNtcLocalMax / 16;
+    // (a small cell has at most kNtcMidMax candidates, a share about 16 or more)
+    constexpr int64_t kSharesPerCell = kNtcMidMax / 16;
     l.n_cell = n_cells < kNtcCellBlocks / kSharesPerCell ? n_cells * kSharesPerCell : kNtcCellBlocks;
     l.n_pb = n_cells < 2048 ? n_cells : 2048;
     l.n_seg = (cap + kNtcSeg - 1) / kNtcSeg;
@@ -1177,8 +1212,8 @@ static NtcLayout ntc_layout(int64_t n_cells, int64_t cap) {
     l.b_off = l.b_count;
     l.b_pmax = l.b_count;
     l.b_i32c = align256(4 * nc);
-    l.b_piece = align256(8 * ((nc + kNtcPiece - 1) / kNtcPiece));
-    l.b_bsum = align256(16 * (size_t)l.nb);
+    l.b_piece = align256(sizeof(int4) * ((nc + kNtcPiece - 1) / kNtcPiece));
+    l.b_bsum = align256(24 * (size_t)l.nb);
     l.b_cpart = align256(sizeof(NtcPart) * (size_t)(l.n_cell > 0 ? l.n_cell : 1));
     l.b_ctl = align256(sizeof(NtcCtl));
     l.cell = l.b_ctl + l.b_count + l.b_off + l.b_pmax + 3 * l.b_i32c + l.b_piece + l.b_bsum + l.b_cpart;
@@ -1293,7 +1328,7 @@ struct NtcQueue {
         int32_t* pending = (int32_t*)(cw += l.b_pmax);
         int32_t* large = (int32_t*)(cw += l.b_i32c);
         int32_t* pend = (int32_t*)(cw += l.b_i32c);
-        int2* piece = (int2*)(cw += l.b_i32c);
+        int4* piece = (int4*)(cw += l.b_i32c);
         long long* bsum = (long long*)(cw += l.b_piece);
         cell_part = (NtcPart*)(cw += l.b_bsum);
         head = (NtcHead*)s.touch;
@@ -1308,9 +1343,8 @@ struct NtcQueue {
                 (const T*)e.w, (const T*)g.w, off_e, off_g, n_cells, e.n, g.n, dt, dn, seed, step, head,
                 dev_step ? 1 : 0, count, p_max, pending);
         }
-        a.local = ntc_local(n_cells);
-        k_ntc_scan<<<(unsigned)l.nb, kNtcThreads, 0, st>>>(count, n_cells, a.local, piece, bsum, large, cap, ctl, head,
-                                                           touch, 2 * (s.cap_e + s.cap_g), (NtcCtl*)host);
+        k_ntc_scan<<<(unsigned)l.nb, kNtcThreads, 0, st>>>(count, n_cells, piece, bsum, large, cap, ctl, head, touch,
+                                                           2 * (s.cap_e + s.cap_g), (NtcCtl*)host);
         if (host) {
             const hipError_t err = hipEventRecord(ev, st);
             if (err != hipSuccess) return err;
@@ -1365,7 +1399,7 @@ struct NtcQueue {
     }
 
     void large() {
-        if (a.n_cells <= 0 || cap <= a.local) return;  // (no cell can have more than the capacity)
+        if (a.n_cells <= 0 || cap <= kNtcLow) return;  // (no cell can have more than the capacity: none is large)
         k_ntc_pick<T><<<(unsigned)l.n_pb, kNtcThreads, 0, st>>>(a);
         // one workgroup per segment, up to the capacity; kNtcSub smaller ones per segment
         k_ntc_eval<T><<<(unsigned)l.n_seg, kNtcSeg, 0, st>>>(a);

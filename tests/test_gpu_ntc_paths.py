@@ -1,6 +1,6 @@
-"""Which way the no-time-counter step takes a cell: one wave up to a number of
-candidates that falls with the cell count, the kernels of the large cells
-beyond, queued before or after the counts are known; and the largest weight of
+"""Which way the no-time-counter step takes a cell: one wave up to 64 candidates,
+the kernels of the large cells beyond 256, queued before or after the counts are
+known, and between the two by the cells that there are; and the largest weight of
 cells far longer than the average.  Against the FP64 oracle element by element,
 with the metric and tolerances of the no-time-counter tests."""
 import numpy as np
@@ -12,18 +12,37 @@ from tests.test_gpu_ntc import _cells_plasma, _chain_compare, _gpu_steps, ctx  #
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_cells, local", [(7, 64), (8, 128), (639, 128), (640, 192), (1279, 192), (1280, 256)])
-def test_cells_at_the_limit(ctx, orc, n_cells, local):  # noqa: F811
-    """Cells of exactly the limit, one candidate fewer and one more (unit
-    probability bound: N_e N_g candidates), and small ones around them."""
-    ne, ng = np.full(n_cells, 2), np.full(n_cells, 3)
-    at = [0, n_cells // 2, n_cells - 1]
-    ne[at[0]], ng[at[0]] = 8, local // 8
-    ne[at[1]], ng[at[1]] = 1, local - 1
-    ne[at[2]], ng[at[2]] = 1, local + 1
+def _products(want):
+    """(N_e, N_g) with the given products, neither larger than need be (1 and 0
+    for 0)."""
+    ne = np.array([max(d for d in range(1, max(2, int(w ** 0.5) + 1)) if w % d == 0) for w in want])
+    return ne, np.asarray(want) // ne
+
+
+@pytest.mark.parametrize("n_cells, n_mid, most", [(7, 2, 100), (8, 2, 128), (8, 2, 129), (700, 0, 0), (700, 639, 128),
+                                                 (700, 639, 129), (700, 639, 256), (700, 640, 256),
+                                                 (700, 3, 257), (639, 3, 257), (639, 0, 300), (90, 40, 129),
+                                                 (3000, 700, 257)])
+def test_cells_at_the_limits(ctx, orc, n_cells, n_mid, most):  # noqa: F811
+    """Cells of 64 candidates and of one more, and n_mid cells in all between
+    there and 256, the densest cell with `most` (unit probability bound: N_e N_g
+    candidates): the ways that the middle cells go by their number, by the
+    densest among them, by a denser one, and with few cells."""
+    rng = np.random.default_rng(n_cells + n_mid + most)
+    want = rng.integers(1, 12, n_cells)
+    cells = rng.permutation(n_cells)
+    want[cells[:n_mid]] = rng.integers(65, min(most, 128) + 1, n_mid) if n_mid else 0
+    if n_mid:
+        want[cells[0]] = 65
+    if most > 64:
+        want[cells[1 if most <= 256 else n_mid]] = most
+    want[cells[-1]] = 64
+    want[cells[-3:-1]] = 0  # (cells without one of the species)
+    ne, ng = _products(want)
     p = _cells_plasma(ne, ng, 1.0, 31 + n_cells, heavy=4.0)
     for st, gst, diag in _chain_compare(ctx, orc, p, [0, 1]):
-        assert np.array_equal(np.bincount(diag["cell"], minlength=n_cells), ne * ng)
+        per_cell = np.bincount(diag["cell"], minlength=n_cells)
+        assert np.array_equal(per_cell, want) and np.sum((per_cell > 64) & (per_cell <= 256)) == n_mid
         assert st["n_collided"] > 0
 
 
