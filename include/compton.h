@@ -210,13 +210,15 @@ CS_API cs_status cs_check_layout(cs_ctx* ctx, const int64_t* off, int64_t n_cell
  * sum of P / P_max over valid candidates (the expected collision count),
  * energy sums as cs_compton_step.
  *
- * The call queues the whole step, then waits until the step's candidate
- * count is known on the device (the rest of the step runs meanwhile): the
- * launches are sized for the context's candidate capacity, and a step that
- * draws more candidates than that changes nothing, so the call grows the
- * capacity and queues the step again (this happens on the first call and
- * whenever the count grows past the capacity, which is then set 25% above
- * the count).  The context keeps the scratch: about 60 bytes per candidate
+ * The call queues the step, then waits until its candidate count is known
+ * on the device (the cells of few candidates are resolved meanwhile).  Cells
+ * of many candidates have kernels of their own: queued with the rest when
+ * the context's last step had such cells, after that wait when only this one
+ * has, and not at all where none has.  The launches are sized for the
+ * context's candidate capacity, and a step that draws more candidates than
+ * that changes nothing, so the call grows the capacity and queues the step
+ * again (this happens on the first call and whenever the count grows past
+ * the capacity, which is then set 25% above the count).  The context keeps the scratch: about 60 bytes per candidate
  * of capacity, 300 per cell, and 32 per particle (tags that persist
  * across calls).
  * Errors: CS_ERR_INVALID_ARG (NULL arrays with n > 0, NULL offsets,
@@ -305,8 +307,8 @@ CS_API cs_status cs_pnet_forward(cs_ctx* ctx, const float* params, const float* 
  * mean |y' - t|, mean (y' - t)^2 / 2) with respect to the parameters into
  * grad_out (CS_PNET_PARAMS), and the loss into *loss_out (device scalar, may
  * be NULL).  Per-pair contributions are summed in a fixed order (the result
- * does not depend on timing).  The context keeps a scratch of about 5.3 n
- * bytes up to 1.4 MB, grown on demand (a growth synchronises `stream`). */
+ * does not depend on timing).  The context keeps a scratch of about 10.6 n
+ * bytes up to 2.8 MB, grown on demand (a growth synchronises `stream`). */
 CS_API cs_status cs_pnet_grad(cs_ctx* ctx, const float* params, const float* in, const float* target, int64_t n,
                        cs_loss loss, float* grad_out, float* loss_out, void* stream);
 
@@ -417,15 +419,15 @@ typedef enum {
     CS_OPT_CHUNKS_PER_BLOCK = 1, /* fused: 256-pair chunks per workgroup; compact: the  */
                                  /* pair kernel's chunks per workgroup (rounded up to a  */
                                  /* multiple of the pairs per lane, at most 32);         */
-                                 /* 0 = automatic (compact: the fewest with which every  */
-                                 /* pair workgroup is resident on the device at once)    */
+                                 /* 0 = automatic (at most 32; every workgroup resident  */
+                                 /* on the device at once if that many do, for compact   */
+                                 /* with the evenest load of the compute units)          */
     CS_OPT_PAIRS_PER_LANE = 2,   /* compact: chunks each lane of the pair kernel takes   */
                                  /* at a time (1, 2 or 4), 0 = automatic (1)             */
-    CS_OPT_WIDE_INDEX = 3        /* compact: 0 (default) = the pair kernel reads the     */
-                                 /* particles with 32-bit byte offsets whenever each     */
-                                 /* species has at most 2^32 / element-size entries,     */
-                                 /* 64-bit indexing otherwise; 1 = 64-bit indexing       */
-                                 /* always (same results)                                */
+    CS_OPT_WIDE_INDEX = 3        /* fused and compact: 0 (default) = particles are read  */
+                                 /* with 32-bit byte offsets whenever each species has   */
+                                 /* at most 2^32 / element-size entries, 64-bit indexing */
+                                 /* otherwise; 1 = 64-bit indexing always (same results) */
 } cs_option;
 
 /* Set / read a context option.  CS_ERR_INVALID_ARG for unknown options or

@@ -244,8 +244,8 @@ class Context:
 
     def ntc_step(self, e, g, off_e, off_g, dt, density_norm, seed, step, stats=None, stream=None):
         """One Compton step with no-time-counter candidate selection, in place
-        on device tensors (the layout of step); queues the whole step, then
-        waits for the device's candidate count."""
+        on device tensors (the layout of step); waits for the device's
+        candidate count."""
         code = _dtype_code(e["x"])
         rc = lib().cs_ntc_step(self._h, code, _species(e), _species(g), _ptr(off_e), _ptr(off_g),
                                off_e.numel() - 1, float(dt), float(density_norm), int(seed), int(step), _ptr(stats),

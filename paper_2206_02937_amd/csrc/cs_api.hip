@@ -293,9 +293,9 @@ Plan plan_step(int64_t strategy, int64_t chunks_per_block, int64_t pairs_per_lan
         pl.bytes = cs::fused_workspace_bytes(sh);
     } else if (strategy == CS_STRATEGY_COMPACT) {
         // pair workgroups take G consecutive chunks, a multiple of the pairs
-        // per lane and at most kCompactMaxChunks (chunk_cell held one entry
-        // per lane); automatic: compact_fit_chunks (every pair workgroup
-        // resident at once: one round, the waves paced)
+        // per lane and at most kCompactMaxChunks; automatic:
+        // compact_fit_chunks (every pair workgroup resident at once: one round,
+        // the waves paced)
         const int64_t ppl = sh.pairs_per_lane;
         int64_t Gc = chunks_per_block > 0 ? chunks_per_block : cs::compact_fit_chunks(dtype, ppl, sh.n_chunks);
         Gc = (Gc + ppl - 1) / ppl * ppl;

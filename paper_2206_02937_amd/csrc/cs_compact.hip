@@ -109,9 +109,11 @@ __device__ __forceinline__ void balance_priority(int rem) {
 // places the workgroup's slots (wave 0's, then wave 1's, ...) in the dense
 // list, whose entry q names the stash slot of accepted pair q.
 //
-// Bound by the vector instructions (about 80 % of a compute unit's busy
-// time), 224 per 64 pairs with 256-pair cells and 381 with ragged 64-pair
-// ones (292 and 507 before); the pairing and the reads are 25 of its 41 us at 2^22 pairs.  At 80
+// Bound by issuing the vector instructions, 224 per 64 pairs with 256-pair cells
+// and 381 with ragged 64-pair ones (292 and 507 before): about 0.7 of the cycles
+// on the grid, 0.8 on uneven cells.  On 2^24 pairs, beyond the caches, it is half
+// of the cycles and 0.55 of a large copy's rate, neither a limit by itself.  The
+// pairing and the reads are 25 of its 41 us at 2^22 pairs.  At 80
 // vector registers six waves fit a SIMD (five at 91, with log1p's constants
 // in s(x)).  FP32 storage, plain sampler: 2^22 pairs in 256-pair cells 46.1 ->
 // 41.2 us, in 64-pair cells of uneven filling 85.5 -> 68.7 us, 2^24 pairs

@@ -394,7 +394,7 @@ __device__ __forceinline__ float icdf_start(float w, float x, float target) {
     return v - 2.0f * R * f * __builtin_amdgcn_rcpf(fmaf(R * iA * iA, g, 2.0f * f * f));
 }
 
-// The same for x < kSmallX: starting value w (A(w) + x B(w)) (6e-4), then a
+// The same for x < kSmallX: starting value w (A(w) + x B(w)) (8e-4), then a
 // Newton step on the tail and its density as polynomials to second order in x.
 __device__ __forceinline__ float icdf_start_small(float w, float x, float target) {
     float v = w * fmaf(x, horner_f32<kStartSmallB>(kStartB, w), horner_f32<kStartSmallA>(kStartA, w));
@@ -464,11 +464,12 @@ __device__ __attribute__((noinline)) double icdf_refine(double v, double x, doub
 //
 // What bounds it: VALU issue, about four cycles per wave and instruction in
 // FP32 and FP64 alike, so the number of instructions counts, whatever their
-// type: 397 per wave with x over [1e-8, 1e3] in every wave, 138 where all
-// are below kSmallX.  k_sample_plain on 2^22 FP32 samples of the former:
+// type: 420 per wave with x over [1e-8, 1e3] in every wave, 135 where all
+// are below kSmallX, 731 over [1e3, 1e6], where icdf_refine answers.
+// k_sample_plain on 2^22 FP32 samples of the first:
 // 176.4 us with three series up to 30 terms for the tail below x = 1, its
 // closed form above, and 2-4 FP64 Halley steps from the Thomson root;
-// 42.8 us with this (22.6 us for the power-law plasma's inputs, 50.2 before).
+// 44.7 us with this (22.6 us for the power-law plasma's inputs, 50.2 before).
 // The two starts part at kSmallX because the cheap one needs the tail's
 // expansion in x; the whole grid range on icdf_start alone would slow the
 // small-x plasmas to its cost.

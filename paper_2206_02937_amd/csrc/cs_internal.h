@@ -82,7 +82,7 @@ struct StepShape {
     int64_t chunks_per_block;  // fused / compact pair kernel: consecutive chunks per workgroup
     int64_t n_step_blocks;     // fused: grid of k_step (>= 1)
     int64_t n_prep_blocks;     // fused / compact: grid of k_prep_scan
-    int64_t n_dense_blocks;    // compact: grid of the one-wave collide kernel
+    int64_t n_dense_blocks;    // compact: grid of the collide kernel (four waves each)
     int64_t pairs_per_lane;    // compact: chunks each pair-kernel lane takes at a time (1, 2, 4)
 };
 
@@ -172,7 +172,7 @@ struct StepParams {
     cs_stats* stats;
     hipEvent_t* events;   // CS_STAGE_COUNT + 1 events to record between stages, or nullptr
     int use_device_step;  // 1: kernels take the step from the device counter (graph replay)
-    int wide_index;       // compact pair kernel: 1 = 64-bit particle indexing even where 32-bit offsets fit
+    int wide_index;       // fused and compact: 1 = 64-bit particle indexing even where 32-bit offsets fit
 };
 
 // Launch every kernel of one step on `stream`; returns the HIP error of the
@@ -301,7 +301,7 @@ struct cs_ctx {
     int64_t strategy = CS_STRATEGY_FUSED;
     int64_t chunks_per_block = 0;  // 0: automatic
     int64_t pairs_per_lane = 0;    // compact pair kernel, 0: automatic
-    int64_t wide_index = 0;        // compact pair kernel, 1: always 64-bit particle indexing
+    int64_t wide_index = 0;        // fused and compact, 1: always 64-bit particle indexing
     std::string last_error;
     bool timing = false;
     int64_t timed_steps = 0;          // steps timed since enabling or the last read

@@ -312,7 +312,7 @@ __device__ __forceinline__ void mlp_tile(const typename FragT<PREC>::type* frag,
 // the vector ALUs.  What bounds it: the FP32 matrix rate (768 products of 32
 // cycles per 64 samples) and SiLU on the vector ALUs (256 per sample), which
 // overlap little: 2^22 samples 1552 us with single-float fragment reads and
-// the IEEE quotient, 1314 us with this.  In the collide kernel it replaced one
+// the IEEE quotient, 1235 us with this.  In the collide kernel it replaced one
 // sample per lane on the vector ALUs (65 KB of LDS for the activations):
 // 107 us -> 34 us on the beam-gas plasma of 2^20 pairs (16 k collisions).
 constexpr int kF32Frag = 3 * 4 * 4 * 64;  // 16-byte entries [layer][T][t][lane], 48 KB

@@ -82,6 +82,7 @@ constexpr int kNtcScanPer = 4;                            // cells per thread in
 constexpr int kNtcScanBlock = kNtcThreads * kNtcScanPer;  // cells per scan workgroup
 constexpr int kNtcPiece = 16;                             // cells per piece: 64 pieces per scan workgroup
 static_assert(kNtcScanBlock == 64 * kNtcPiece, "a wave reads a scan workgroup's pieces at once");
+
 // Which cells are resolved by one wave each (k_ntc_cells), which by the kernels
 // of the large cells.  A wave takes a cell's candidates 64 at a time in turn, those
 // kernels take all at once over the chip, in seven launches more.  Up to kNtcLow
@@ -768,8 +769,8 @@ __device__ __forceinline__ const NtcArgs<T>* ntc_own_args() {
 // of the arrays) 16, the first round's scattering 15 and its writes 7, the
 // later rounds 19.  As kernels of their own -- picks, evaluation, collisions,
 // two rounds, the serial rest, the sums -- it was 112 us.  Workgroups of four
-// waves with windows of 512 and barriers between the phases: 96.  Shares of 104,
-// 128 and 160 candidates: 71, 67 and 65.
+// waves with windows of 512 and barriers between the phases: 96.  With shares of
+// 104 or 128 candidates it takes 9 and 3 % longer than with 160.
 constexpr int kNtcCellBlocks = 4096;
 constexpr int kNtcShare = 160;  // most candidates of a share
 static_assert(kNtcShare <= 256, "8-bit indices of a group's cells");
@@ -1201,7 +1202,8 @@ static NtcLayout ntc_layout(int64_t n_cells, int64_t cap) {
     NtcLayout l;
     l.nb = (n_cells + kNtcScanBlock - 1) / kNtcScanBlock;
     if (l.nb < 1) l.nb = 1;  // (a step without cells too)
-    // (a small cell has at most kNtcMidMax candidates, a share about 16 or more)
+    // (a small cell has at most kNtcMidMax candidates, a share 14 or more; waves
+    // take groups in grid strides, so that any number of them is right)
     constexpr int64_t kSharesPerCell = kNtcMidMax / 16;
     l.n_cell = n_cells < kNtcCellBlocks / kSharesPerCell ? n_cells * kSharesPerCell : kNtcCellBlocks;
     l.n_pb = n_cells < 2048 ? n_cells : 2048;
