@@ -48,8 +48,9 @@ __global__ __launch_bounds__(kPnetThreads) void k_pnet_target(const float* in, i
 // The parameters are the same for every lane and do not change while a kernel
 // runs, so they are read through the constant address space: scalar loads,
 // and each multiply-add takes its weight from a scalar register.  (From LDS,
-// the 337 broadcast reads per wave kept the LDS busy twice as long as the
-// multiply-adds kept the vector ALUs.)
+// the 337 broadcast reads per wave keep the LDS busy twice as long as the
+// multiply-adds keep the vector ALUs; k_pnet_fwd uses them all the same where
+// there are too few waves to wait for scalar loads.)
 typedef const __attribute__((address_space(4))) float* cfptr;
 
 // The forward pass of one pair: pre-activations and activations kept for the
@@ -59,7 +60,8 @@ struct PnetActs {
     float y;
 };
 
-__device__ __forceinline__ void pnet_forward(cfptr P, PnetActs& s) {
+template <typename Params>
+__device__ __forceinline__ void pnet_forward(Params P, PnetActs& s) {
 #pragma unroll
     for (int m = 0; m < 9; ++m) {
         float z = P[kB1 + m];
@@ -90,13 +92,34 @@ __device__ __forceinline__ void pnet_forward(cfptr P, PnetActs& s) {
 // A pair's nine inputs (rows of 36 bytes, 4-byte aligned).
 __device__ __forceinline__ void load_pair(const float* row, float (&x)[9]) { __builtin_memcpy(x, row, sizeof(x)); }
 
+// Pairs from and up to which the parameters come from LDS (LDS true) and not by
+// scalar loads: eight waves per SIMD are 2^19 pairs, and the waves of a second
+// round that is not full have too few others beside them.  Analytic ratio and
+// forward together, us, by LDS / by scalar loads: 500,000 pairs 15.4 / 15.9, 700,000
+// 19.4 / 19.7, 2^20 25.5 / 25.4, 1.2 M 32.1 / 30.3, 2^22 97.7 / 89.9; the forward
+// alone 300,000 6.5 / 5.9.  (Loads of a pair that is clamped, not left out, past
+// the end made the scalar form 0.3-0.9 us longer.)
+constexpr int64_t kPnetLdsMin = 3 << 17, kPnetLdsMax = 1 << 20;
+
+template <bool LDS>
 __global__ __launch_bounds__(kPnetThreads) void k_pnet_fwd(const float* params, const float* in, int64_t n,
                                                          float* y) {
     const int64_t i = (int64_t)blockIdx.x * kPnetThreads + threadIdx.x;
     PnetActs s;
-    load_pair(in + 9 * (i < n ? i : n - 1), s.a0);
-    pnet_forward((cfptr)params, s);
-    if (i < n) y[i] = s.y;
+    if constexpr (LDS) {
+        __shared__ float s_p[kPnetParams];
+        for (int q = threadIdx.x; q < kPnetParams; q += kPnetThreads) s_p[q] = params[q];
+        __syncthreads();
+        if (i >= n) return;
+#pragma unroll
+        for (int q = 0; q < 9; ++q) s.a0[q] = in[9 * i + q];
+        pnet_forward((const float*)s_p, s);
+    } else {
+        if (i >= n) return;
+        load_pair(in + 9 * i, s.a0);
+        pnet_forward((cfptr)params, s);
+    }
+    y[i] = s.y;
 }
 
 // Weight gradient of one layer over a wave's 64 pairs: acc[o][i] += sum over
@@ -334,7 +357,8 @@ hipError_t launch_pnet_target(const float* in, int64_t n, float* y, hipStream_t 
 
 hipError_t launch_pnet_forward(const float* params, const float* in, int64_t n, float* y, hipStream_t st) {
     if (n > 0)
-        k_pnet_fwd<<<(unsigned)((n + kPnetThreads - 1) / kPnetThreads), kPnetThreads, 0, st>>>(params, in, n, y);
+        (n > kPnetLdsMin && n <= kPnetLdsMax ? k_pnet_fwd<true> : k_pnet_fwd<false>)
+            <<<(unsigned)((n + kPnetThreads - 1) / kPnetThreads), kPnetThreads, 0, st>>>(params, in, n, y);
     return hipGetLastError();
 }
 
